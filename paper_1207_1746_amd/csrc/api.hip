@@ -493,19 +493,16 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
             gk::LArgs la;
             memset(&la, 0, sizeof la);
             la.g = geo_of(g0);
-            la.ndim = g0->d.ndim;
             la.nin = n_in;
             la.nout = n_out;
-            la.nterms = op->nterms;
             int radius[16] = {0};
             for (int t = 0; t < op->nterms; ++t) {
                 const gscl_term& tm = op->terms[t];
                 if (tm.grid < 0 || tm.grid >= n_in || tm.out < 0 || tm.out >= n_out || tm.coef < -1 || tm.coef >= n_in)
                     return gscl_fail(GSCL_ERR_ARG, "term %d references a missing grid", t);
-                if (la.ndim == 2 && tm.dz != 0) return gscl_fail(GSCL_ERR_ARG, "term %d: dz must be 0 in 2D", t);
+                if (g0->d.ndim == 2 && tm.dz != 0) return gscl_fail(GSCL_ERR_ARG, "term %d: dz must be 0 in 2D", t);
                 const int r = std::max(std::abs(tm.dx), std::max(std::abs(tm.dy), std::abs(tm.dz)));
                 radius[tm.grid] = std::max(radius[tm.grid], r);
-                la.t[t] = gk::LinTerm{tm.out, tm.grid, tm.dx, tm.dy, tm.dz, tm.coef, tm.w};
             }
             for (int i = 0; i < n_in; ++i) {
                 if (in[i]->d.halo < radius[i])
@@ -520,9 +517,26 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
                 la.bcv[i] = in[i]->d.bc_value;
                 la.in[i] = in[i]->ptr;
             }
-            for (int o = 0; o < n_out; ++o) la.out[o] = out[o]->ptr;
+            // offsets are within the declared halos (0..4) from here on
+            int nt = 0;
+            for (int o = 0; o < n_out; ++o) {
+                la.out[o] = out[o]->ptr;
+                for (int t = 0; t < op->nterms; ++t) {
+                    const gscl_term& tm = op->terms[t];
+                    if (tm.out != o) continue;
+                    const int64_t off = tm.dz * la.g.pz + tm.dy * la.g.py + tm.dx;
+                    la.t[nt++] = gk::LinTerm{(const char*)in[tm.grid]->ptr + off * (int64_t)dtype_size(dt), tm.w,
+                                             tm.grid | (tm.coef + 1) << 8,
+                                             (tm.dx & 255) | (tm.dy & 255) << 8 | (tm.dz & 255) << 16};
+                    la.rx = std::max(la.rx, std::abs(tm.dx));
+                    la.ry = std::max(la.ry, std::abs(tm.dy));
+                    la.rz = std::max(la.rz, std::abs(tm.dz));
+                }
+                la.tend[o] = nt;
+            }
             la.operand = red ? fused->operand : 0;
             if (red) {
+                // an upper bound: the launch has at most one block per 64 x 4 points
                 const int64_t nb = ((la.g.nx + 63) / 64) * (int64_t)((la.g.ny + 3) / 4) * la.g.nz;
                 if ((rc = take_partials(c, fx, nb))) return rc;
                 fill_red(c, fused, la.ra, fx);

@@ -85,22 +85,28 @@ hipError_t launch_wjacobi_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStre
 hipError_t launch_rbgs_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
 int tb_blocks(const Geo& g, int k, int cz);
 
-// Generic linear operator (any offsets, per-grid boundary rule).
+// Generic linear operator (any offsets, per-grid boundary rule).  The terms are
+// ordered by output (the caller's order within one); tend[o] ends output o's.
 struct LinTerm {
-    int out, grid, dx, dy, dz, coef;
+    const void* src;       // the grid's element (dx, dy, dz): in[grid] shifted by the offset
     double w;
+    int32_t grid;          // bits 0..7 the grid, bits 8..15 the coefficient grid + 1 (0: none)
+    int32_t d;             // dx, dy, dz as signed bytes 0..2
 };
 struct LArgs {
     Geo g;                 // extents and pitches (bc fields unused)
-    int ndim;
-    int nin, nout, nterms;
+    int nin, nout;
+    int rx, ry, rz;        // widest |dx|, |dy|, |dz| of any term
+    int nxt, nyt, strip;   // x tiles, row groups, row groups per strip (set at launch)
+    int nblocks;
+    int tend[8];
     int bc[16];
     double bcv[16];
     const void* in[16];
     void* out[8];
-    LinTerm t[64];
     int operand;
     RedArgs ra;
+    LinTerm t[64];
 };
 hipError_t launch_linear(LArgs& a, int dtype, bool red, hipStream_t s, int* nblocks);
 
