@@ -257,10 +257,15 @@ gk::TileCfg pick_tile(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d)
         t.cz = (int)std::max<int64_t>(1, std::min<int64_t>(cz, std::max<int64_t>(d.n[2], 1)));
         return t;
     }
-    if (kind == GSCL_K_IMG_BOX5_LAP) {  // rows per block of the image kernel (measured best: 8)
+    if (kind == GSCL_K_IMG_BOX5_LAP) {
+        // rows per wave of the image kernel: 4 where that leaves every SIMD
+        // several waves, fewer on small images, where a wave's march is one
+        // row's latency per step (4 x 8192^2: 8 rows 232 us, 4 rows 226, 2
+        // rows 273; 1920 x 1080: 8 rows 11.8 us, 4 rows 7.7, 2 rows 6.6)
+        const int64_t rows = (nx + 1023) / 1024 * d.n[1] * d.n[2];
         t.V = 4;
         t.NW = 4;
-        t.cz = 8;
+        t.cz = rows >= 8192 ? 4 : (rows >= 4096 ? 2 : 1);
         return t;
     }
     const bool r2 = kind == GSCL_K_VC13_APPLY || kind == GSCL_K_VC13_JACOBI || kind == GSCL_K_VC13_RESID;
