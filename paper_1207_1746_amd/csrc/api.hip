@@ -243,17 +243,15 @@ gk::TileCfg pick_tile(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d)
     gk::TileCfg t;
     const int64_t nx = d.n[0];
     if (kind == GSCL_K_WJACOBI_TB || kind == GSCL_K_RBGS_TB) {
-        // output planes per block (measured on MI355X from 64^3 to 512^3): the
-        // largest power of two up to (output tiles per plane) * nz / 160 in
-        // FP64 and / 320 in FP32, within 1..64 -- long enough to amortize the
-        // 2k warm-up planes, short enough for about one resident block per
-        // block slot on mid-size grids (FP32 fits two blocks per CU)
+        // nominal output planes per block: the largest power of two up to
+        // (output tiles per plane) * nz / 160 in FP64 and / 320 in FP32, within
+        // 1..64 (a launch balances its chunks over the CUs: tb_chunk)
         const int64_t cols = ((nx + 55) / 56) * ((d.n[1] + 23) / 24);
         const int64_t want = std::max<int64_t>(1, cols * d.n[2] / (dtype == GSCL_F32 ? 320 : 160));
         int64_t cz = 1;
         while (cz * 2 <= want && cz < 64) cz *= 2;
         t.V = 1;
-        t.NW = gk::TB_NW;
+        t.NW = 16;  // fixed shape: row pairs of a block's region
         t.cz = (int)std::max<int64_t>(1, std::min<int64_t>(cz, std::max<int64_t>(d.n[2], 1)));
         return t;
     }
@@ -316,7 +314,7 @@ extern "C" int gscl_tile_set(gscl_ctx* c, int kind, const gscl_grid_desc* gd, co
     int rc = resolve_layout(&d);
     if (rc) return rc;
     c->tiles[std::make_tuple(kind, d.dtype, d.n[0], d.n[1], d.n[2])] =
-        shape_fixed ? gk::TileCfg{1, gk::TB_NW, t->cz} : gk::TileCfg{t->V, t->NW, t->cz};
+        shape_fixed ? gk::TileCfg{1, 16, t->cz} : gk::TileCfg{t->V, t->NW, t->cz};
     return GSCL_OK;
 }
 
@@ -431,6 +429,34 @@ static int take_partials(gscl_ctx* c, const FixedScratch* fx, int64_t nblocks) {
                          "(use gscl_do_all for this grid)",
                          (long long)nblocks, GSCL_NOALLOC_PARTIALS);
     return GSCL_OK;
+}
+
+// z chunk of a blocked pass: the one set for these extents, else the one that
+// balances the blocks over the chip.  A fused reduction takes a partial per
+// block: the choice never needs more than the nominal chunk does or 2048, and
+// a call into the fixed scratch is refused by the count its limit has always
+// been held against, that of nominal chunks of tiles with exactly k ghost
+// columns.
+static int tb_chunk(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d, const gk::Geo& g, int k) {
+    const int nominal = pick_tile(c, kind, dtype, d).cz;
+    if (c->tiles.count(std::make_tuple(kind, dtype, d.n[0], d.n[1], d.n[2]))) return nominal;
+    const int64_t most = std::max<int64_t>(gk::tb_blocks(g, k, nominal), 2048);
+    const int cz = gk::tb_pick_chunk(g.nz, most, kind == GSCL_K_RBGS_TB, dtype == GSCL_F64, k,
+                                     [&](int q) { return gk::tb_blocks(g, k, q); });
+    return cz ? cz : nominal;
+}
+
+static int tb_partials(gscl_ctx* c, const FixedScratch* fx, int kind, int dtype, const gscl_grid_desc& d,
+                       const gk::Geo& g, int k, int& cz) {
+    if (fx) {
+        const int nominal = pick_tile(c, kind, dtype, d).cz, ox = gk::TB_COLS - 2 * k, oy = gk::TB_ROWS - 2 * k;
+        const int rc = take_partials(c, fx, (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) *
+                                                ((g.nz + nominal - 1) / nominal));
+        if (rc) return rc;
+        while (gk::tb_blocks(g, k, cz) > GSCL_NOALLOC_PARTIALS) ++cz;  // (a few tiles more at odd k)
+        return GSCL_OK;
+    }
+    return take_partials(c, fx, gk::tb_blocks(g, k, cz));
 }
 
 static void fill_red(gscl_ctx* c, const gscl_reduce_desc* rd, gk::RedArgs& ra, const FixedScratch* fx = nullptr) {
@@ -628,10 +654,9 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
             ta.p[2] = 1.0 / op->p[1];
             ta.k = (int)kd;
             ta.operand = red ? fused->operand : 0;
-            gk::TileCfg t = pick_tile(c, op->kind, dt, g0->d);
-            ta.cz = t.cz;
+            ta.cz = tb_chunk(c, op->kind, dt, g0->d, ta.g, ta.k);
             if (red) {
-                if ((rc = take_partials(c, fx, gk::tb_blocks(ta.g, ta.k, ta.cz)))) return rc;
+                if ((rc = tb_partials(c, fx, op->kind, dt, g0->d, ta.g, ta.k, ta.cz))) return rc;
                 fill_red(c, fused, ta.ra, fx);
             }
             he = gk::launch_wjacobi_tb(ta, dt == GSCL_F64 ? 0 : 1, n_in == 2, red, c->stream, &nblocks);
@@ -664,10 +689,9 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
             ta.p[3] = op->p[2];
             ta.k = (int)kd;
             ta.operand = red ? fused->operand : 0;
-            gk::TileCfg t = pick_tile(c, op->kind, dt, g0->d);
-            ta.cz = t.cz;
+            ta.cz = tb_chunk(c, op->kind, dt, g0->d, ta.g, ta.k);
             if (red) {
-                if ((rc = take_partials(c, fx, gk::tb_blocks(ta.g, ta.k, ta.cz)))) return rc;
+                if ((rc = tb_partials(c, fx, op->kind, dt, g0->d, ta.g, ta.k, ta.cz))) return rc;
                 fill_red(c, fused, ta.ra, fx);
             }
             he = gk::launch_rbgs_tb(ta, dt == GSCL_F64 ? 0 : 1, n_in == 2, red, c->stream, &nblocks);

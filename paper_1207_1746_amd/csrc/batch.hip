@@ -58,10 +58,24 @@ struct BSlot {
     float* d2;
     float* rh;
     int ntx, nty, ncz, cz;
-    int tile_begin, ntiles;
-    int tntx, tnty, tncz, tcz;   // blocked-pass tiles (sweeps_per_pass > 1)
-    int tb_begin, tb_ntiles;
-    int tb_czmin;                // smallest blocked-pass z chunk of the slot
+    int ntiles;
+    // blocked-pass tiles (sweeps_per_pass > 1): those of passes without a
+    // reduction balance the whole batch over the CUs; those of a reducing pass
+    // depend on the slot alone
+    int tntx, tnty;
+    int tncz, tcz, tb_ntiles;
+    int rncz, rcz, rb_ntiles;
+    int rule_cz;                 // z chunk of the batch's tile rule (0: none)
+};
+
+// Tile lists of a batch: one-sweep tiles, blocked-pass tiles, blocked tiles of
+// reducing passes.
+enum { LIST_ONE = 0, LIST_TB = 1, LIST_RED = 2, LISTS = 3 };
+
+// What finding a tile's slot takes of each slot, compact.
+struct BFind {
+    int begin[LISTS];        // first tile of the slot in each list
+    int id;                  // index into the state array
 };
 
 struct BState {
@@ -74,36 +88,49 @@ struct BState {
 
 struct BHeader {
     int nslots;
-    int total_tiles;
-    int total_tb_tiles;
+    int total[LISTS];
 };
 
 enum { MODE_F64 = 0, MODE_RESID = 1, MODE_F32 = 2, MODE_RBGS = 3, MODE_RBGS_TB = 4 };
 
-// slot owning global tile t (TB: of the blocked-pass tile list)
-template <bool TB = false>
-__device__ __forceinline__ int find_slot(const BSlot* __restrict__ s, int n, int t) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((TB ? s[mid].tb_begin : s[mid].tile_begin) <= t) lo = mid;
-        else hi = mid - 1;
+// Slot owning global tile t of a list, and the tile's index in it; -1 if the
+// slot is not running.  The lanes look at 64 slots at a time (a binary search
+// is a chain of loads, each longer than a step of the march).
+template <int LIST>
+__device__ __forceinline__ int find_slot(const BFind* __restrict__ s, const BState* st, int n, int t, int& local) {
+    const int lane = threadIdx.x & 63;
+    int si = -1, begin = 0;
+    bool running = false;
+    for (int base = 0; base < n; base += 64) {
+        const int i = min(base + lane, n - 1);
+        const int b = s[i].begin[LIST];
+        const uint64_t below = __ballot(base + lane < n && b <= t);
+        if (below == 0) break;
+        const uint64_t run = __ballot(st[s[i].id].state == 1);
+        const int last = 63 - __clzll((long long)below);
+        si = base + last;
+        begin = __builtin_amdgcn_readlane(b, last);
+        running = (run >> last) & 1;
+        if (below != ~0ull) break;
     }
-    return lo;
+    local = t - begin;
+    return running ? __builtin_amdgcn_readfirstlane(si) : -1;
 }
 
 template <int MODE, bool RED>
-__global__ __launch_bounds__(64 * BNW) void batch_sweep(const BSlot* __restrict__ slots, const BState* st,
+__global__ __launch_bounds__(64 * BNW) void batch_sweep(const BSlot* __restrict__ slots,
+                                                        const BFind* __restrict__ find, const BState* st,
                                                         const BHeader* hdr, double* partials, int parity,
                                                         double omega) {
     using OpF64 = gk::OpWJacobi<double, double, 3, true>;
     using OpF32 = gk::OpWJacobi<float, float, 3, true>;
     using OpRB = gk::OpRBGS<double, true>;
-    const int n = hdr->nslots, total = hdr->total_tiles;
+    const int n = hdr->nslots, total = hdr->total[LIST_ONE];
     for (int t = blockIdx.x; t < total; t += gridDim.x) {
-        const int si = find_slot(slots, n, t);
+        int local;
+        const int si = find_slot<LIST_ONE>(find, st, n, t, local);
+        if (si < 0) continue;
         const BSlot& s = slots[si];
-        if (st[s.id].state != 1) continue;
         gk::TArgs a;
         a.g.nx = s.nx;
         a.g.ny = s.ny;
@@ -124,7 +151,6 @@ __global__ __launch_bounds__(64 * BNW) void batch_sweep(const BSlot* __restrict_
         a.ra.result = nullptr;
         a.ra.op = gk::R_SUMSQ;
         a.ra.eps = 0.0;
-        const int local = t - s.tile_begin;
         double acc = 0.0;
         if (MODE == MODE_F64) {
             a.nb[0] = parity ? s.u2 : s.u;
@@ -163,15 +189,17 @@ template <int MODE>
 using BatchT = typename std::conditional<MODE == MODE_F32, float, double>::type;
 
 template <int MODE, bool RED, int K>
-__global__ __launch_bounds__(64 * gk::TB_NW, (gk::tb_waves_per_eu<BatchT<MODE>, K, RED, MODE == MODE_RBGS_TB>()))
-void batch_tb(const BSlot* __restrict__ slots, const BState* st, const BHeader* hdr, double* partials, int parity,
-              double omega) {
+__global__ __launch_bounds__(64 * gk::TB_NW, (gk::tb_waves_per_eu<BatchT<MODE>, K, MODE == MODE_RBGS_TB>()))
+void batch_tb(const BSlot* __restrict__ slots, const BFind* __restrict__ find, const BState* st, const BHeader* hdr,
+              double* partials, int parity, double omega) {
     using T = BatchT<MODE>;
-    const int n = hdr->nslots, total = hdr->total_tb_tiles;
+    constexpr int LIST = RED ? LIST_RED : LIST_TB;
+    const int n = hdr->nslots, total = hdr->total[LIST];
     for (int t = blockIdx.x; t < total; t += gridDim.x) {
-        const int si = find_slot<true>(slots, n, t);
+        int local;
+        const int si = find_slot<LIST>(find, st, n, t, local);
+        if (si < 0) continue;
         const BSlot& s = slots[si];
-        if (st[s.id].state != 1) continue;
         gk::TBArgs a;
         a.g.nx = s.nx;
         a.g.ny = s.ny;
@@ -187,8 +215,8 @@ void batch_tb(const BSlot* __restrict__ slots, const BState* st, const BHeader* 
         a.k = K;
         a.ntx = s.tntx;
         a.nty = s.tnty;
-        a.ncz = s.tncz;
-        a.cz = s.tcz;
+        a.ncz = RED ? s.rncz : s.tncz;
+        a.cz = RED ? s.rcz : s.tcz;
         a.operand = gk::RV_RESIDUAL;
         a.ra.partials = partials;
         a.ra.result = nullptr;
@@ -204,24 +232,25 @@ void batch_tb(const BSlot* __restrict__ slots, const BState* st, const BHeader* 
             a.f = s.f;
         }
         double acc = 0.0;
-        // slots of blocked batches span fewer than 2^32 elements (admission),
-        // so the march keeps 32-bit plane offsets
         constexpr bool RB = MODE == MODE_RBGS_TB;
-        gk::tb7_tile<T, true, K, RED, RB, true>(a, t - s.tb_begin, acc);
+        gk::tb7_tile<T, true, K, RED, RB>(a, local, acc);
+        // the next tile stages into LDS rows that other waves may still read
+        __syncthreads();
         if (RED) gk::block_reduce(acc, a.ra, t);
     }
 }
 
 // u += d and d = 0 over every tile of running slots (refinement update).
-__global__ __launch_bounds__(64 * BNW) void batch_update(const BSlot* __restrict__ slots, const BState* st,
+__global__ __launch_bounds__(64 * BNW) void batch_update(const BSlot* __restrict__ slots,
+                                                         const BFind* __restrict__ find, const BState* st,
                                                          const BHeader* hdr) {
-    const int n = hdr->nslots, total = hdr->total_tiles;
+    const int n = hdr->nslots, total = hdr->total[LIST_ONE];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int t = blockIdx.x; t < total; t += gridDim.x) {
-        const int si = find_slot(slots, n, t);
+        int local;
+        const int si = find_slot<LIST_ONE>(find, st, n, t, local);
+        if (si < 0) continue;
         const BSlot& s = slots[si];
-        if (st[s.id].state != 1) continue;
-        const int local = t - s.tile_begin;
         const int xt = local % s.ntx, rest = local / s.ntx, yt = rest % s.nty, zc = rest / s.nty;
         const int x = xt * 64 + lane, y = yt * BNW + w;
         if (x >= s.nx || y >= s.ny) continue;
@@ -236,7 +265,8 @@ __global__ __launch_bounds__(64 * BNW) void batch_update(const BSlot* __restrict
 
 // Per-slot fold of the residual partials and the stopping rule.
 // tb: the partials come from the blocked-pass tiles.
-__global__ __launch_bounds__(256) void batch_finish(const BSlot* __restrict__ slots, BState* st,
+__global__ __launch_bounds__(256) void batch_finish(const BSlot* __restrict__ slots,
+                                                    const BFind* __restrict__ find, BState* st,
                                                     const BHeader* hdr, const double* partials, double rtol2,
                                                     int sweeps_per_check, long long max_sweeps, int ir, int tb) {
     const int i = blockIdx.x;
@@ -244,7 +274,7 @@ __global__ __launch_bounds__(256) void batch_finish(const BSlot* __restrict__ sl
     const BSlot& s = slots[i];
     BState& b = st[s.id];
     if (b.state != 1) return;
-    const int begin = tb ? s.tb_begin : s.tile_begin, count = tb ? s.tb_ntiles : s.ntiles;
+    const int begin = find[i].begin[tb ? LIST_RED : LIST_ONE], count = tb ? s.rb_ntiles : s.ntiles;
     double a = 0.0;
     for (int k = threadIdx.x; k < count; k += blockDim.x) a += partials[begin + k];
     __shared__ double wp[4];
@@ -329,11 +359,13 @@ struct gscl_batch {
     Arena arena;
     char* arena_mem;
     BSlot* d_slots;
+    BFind* d_find;
     BState* d_state;
     BHeader* d_hdr;
     double* d_partials;
     int64_t partial_cap;
     BSlot* h_slots;     // pinned staging
+    BFind* h_find;      // pinned staging
     BState* h_state;    // pinned
     BHeader* h_hdr;     // pinned
     hipEvent_t upload_done;
@@ -432,10 +464,12 @@ extern "C" int gscl_batch_create(gscl_ctx* c, const gscl_batch_desc* bd, gscl_ba
         gscl_hip_fail(e, w);
         hipFree(b->arena_mem);
         hipFree(b->d_slots);
+        hipFree(b->d_find);
         hipFree(b->d_state);
         hipFree(b->d_hdr);
         hipFree(b->d_partials);
         hipHostFree(b->h_slots);
+        hipHostFree(b->h_find);
         hipHostFree(b->h_state);
         hipHostFree(b->h_hdr);
         hipHostFree(b->h_snap[0]);
@@ -450,11 +484,13 @@ extern "C" int gscl_batch_create(gscl_ctx* c, const gscl_batch_desc* bd, gscl_ba
     if ((e = hipMalloc(&b->arena_mem, arena)) != hipSuccess) return fail(e, "hipMalloc(arena)");
     b->arena.init(b->arena_mem, arena);
     if ((e = hipMalloc(&b->d_slots, sizeof(BSlot) * ms)) != hipSuccess) return fail(e, "hipMalloc");
+    if ((e = hipMalloc(&b->d_find, sizeof(BFind) * ms)) != hipSuccess) return fail(e, "hipMalloc");
     if ((e = hipMalloc(&b->d_state, sizeof(BState) * ms)) != hipSuccess) return fail(e, "hipMalloc");
     if ((e = hipMalloc(&b->d_hdr, sizeof(BHeader))) != hipSuccess) return fail(e, "hipMalloc");
     b->partial_cap = 1 << 16;
     if ((e = hipMalloc(&b->d_partials, sizeof(double) * b->partial_cap)) != hipSuccess) return fail(e, "hipMalloc");
     if ((e = hipHostMalloc(&b->h_slots, sizeof(BSlot) * ms)) != hipSuccess) return fail(e, "hipHostMalloc");
+    if ((e = hipHostMalloc(&b->h_find, sizeof(BFind) * ms)) != hipSuccess) return fail(e, "hipHostMalloc");
     if ((e = hipHostMalloc(&b->h_state, sizeof(BState) * ms)) != hipSuccess) return fail(e, "hipHostMalloc");
     if ((e = hipHostMalloc(&b->h_hdr, sizeof(BHeader))) != hipSuccess) return fail(e, "hipHostMalloc");
     if ((e = hipEventCreateWithFlags(&b->upload_done, hipEventDisableTiming)) != hipSuccess) return fail(e, "hipEventCreate");
@@ -488,57 +524,73 @@ static bool batch_ok(const gscl_batch* b) { return b && b->magic == BATCH_MAGIC;
 
 // Rebuild the compact table (admitted slots in id order, tile prefix sums) and
 // upload it on the context stream.
-// Blocked tiles of a slot: (64 - 2k) x (32 - 2k) outputs; z chunk a power of
-// two up to tiles per plane * nz / 160 (the standalone rule), but at least
-// czmin planes: the slots of a batch fill the chip together, and short chunks
-// pay the 2k warm-up planes of every tile (measured on mixed batches of
-// 32^3..96^3 grids: czmin 16 is best, 2x over 1-4).
-constexpr int TB_CZMIN = 16;
-static void set_tb_tiles(BSlot& s, int kp, int czmin) {
-    const int ox = 64 - 2 * kp, oy = gk::TB_ROWS - 2 * kp;
-    s.tntx = (s.nx + ox - 1) / ox;
-    s.tnty = (s.ny + oy - 1) / oy;
-    const int64_t want = std::max<int64_t>(1, (int64_t)s.tntx * s.tnty * s.nz / 160);
-    int cz = czmin;
+static int tb_cols(const BSlot& s) { return s.tntx * s.tnty; }
+static int chunk_of(const BSlot& s, int cz) { return std::max(1, std::min(cz, s.nz)); }
+
+// Blocked tiles of a slot's reducing passes, which fold its residual: from its
+// own extents (and the batch's rule), so its result is the same among any
+// others.  The z chunk is a power of two up to tiles per plane * nz / 160, but
+// at least 16 planes: the slots of a batch fill the chip together.
+static void set_tb_tiles(BSlot& s, int kp) {
+    s.tntx = (s.nx + gk::tb_out_x(kp) - 1) / gk::tb_out_x(kp);
+    s.tnty = (s.ny + gk::tb_out_y(kp) - 1) / gk::tb_out_y(kp);
+    const int64_t want = std::max<int64_t>(1, (int64_t)tb_cols(s) * s.nz / 160);
+    int cz = s.rule_cz > 0 ? s.rule_cz : 16;
     while (cz * 2 <= want && cz < 64) cz *= 2;
-    s.tcz = std::min(cz, s.nz);
-    s.tncz = (s.nz + s.tcz - 1) / s.tcz;
-    s.tb_ntiles = s.tntx * s.tnty * s.tncz;
+    s.rcz = chunk_of(s, cz);
+    s.rncz = (s.nz + s.rcz - 1) / s.rcz;
+    s.rb_ntiles = tb_cols(s) * s.rncz;
+}
+
+// Blocked tiles of the passes without a reduction, whose tiling changes no
+// result: one chunk for all slots, chosen like a single launch's; a rule's
+// chunk is kept while the batch has at least 512 tiles with it, and is an upper
+// bound after that (the tail of a stream).
+static void balance_tb_tiles(gscl_batch* b) {
+    const bool rb = b->desc.method == GSCL_BATCH_RBGS, f64 = b->desc.precision == GSCL_PREC_F64;
+    auto each = [&](auto&& fn) {
+        for (int id = 0; id < b->desc.max_slots; ++id)
+            if (b->used[id]) fn(b->slot[id]);
+    };
+    auto tiles = [&](auto&& chunk) {
+        int64_t n = 0;
+        each([&](BSlot& s) { n += (int64_t)tb_cols(s) * ((s.nz + chunk(s) - 1) / chunk(s)); });
+        return n;
+    };
+    int nzmax = 1;
+    bool ruled = false;
+    each([&](BSlot& s) {
+        nzmax = std::max(nzmax, s.nz);
+        ruled = ruled || s.rule_cz > 0;
+    });
+    const bool keep = ruled && tiles([](const BSlot& s) { return s.rule_cz > 0 ? chunk_of(s, s.rule_cz) : s.rcz; }) >= 512;
+    auto bounded = [&](const BSlot& s, int cz) { return chunk_of(s, s.rule_cz > 0 ? std::min(s.rule_cz, cz) : cz); };
+    const int cz = gk::tb_pick_chunk(nzmax, INT32_MAX, rb, f64, b->desc.sweeps_per_pass,
+                                     [&](int q) { return tiles([&](const BSlot& s) { return bounded(s, q); }); });
+    each([&](BSlot& s) {
+        s.tcz = keep && s.rule_cz > 0 ? chunk_of(s, s.rule_cz) : bounded(s, cz);
+        s.tncz = (s.nz + s.tcz - 1) / s.tcz;
+        s.tb_ntiles = tb_cols(s) * s.tncz;
+    });
 }
 
 static int upload_table(gscl_batch* b) {
     gscl_ctx* c = b->ctx;
     GSCL_HIP(hipEventSynchronize(b->upload_done));  // staging buffers free again
-    if (b->desc.sweeps_per_pass > 1 && b->desc.precision != GSCL_PREC_F64) {
-        // Refinement batches: the blocked passes carry no reduction, so their
-        // tiling changes no result; when few slots are left (the tail of a
-        // stream), shorter chunks spread the remaining work over more CUs:
-        // halve the minimum chunk until the batch has 512 blocked tiles.
-        for (int shift = 0;; ++shift) {
-            int64_t total = 0;
-            bool all_one = true;
-            for (int id = 0; id < b->desc.max_slots; ++id)
-                if (b->used[id]) {
-                    BSlot& sl = b->slot[id];
-                    const int czmin = std::max(1, sl.tb_czmin >> shift);
-                    all_one = all_one && czmin == 1;
-                    set_tb_tiles(sl, b->desc.sweeps_per_pass, czmin);
-                    total += sl.tb_ntiles;
-                }
-            if (total >= 512 || all_one) break;
-        }
-    }
-    int n = 0, tiles = 0, tb_tiles = 0;
+    if (b->desc.sweeps_per_pass > 1) balance_tb_tiles(b);
+    int n = 0, total[LISTS] = {0, 0, 0};
     for (int id = 0; id < b->desc.max_slots; ++id) {
         if (!b->used[id]) continue;
-        BSlot s = b->slot[id];
-        s.tile_begin = tiles;
-        tiles += s.ntiles;
-        s.tb_begin = tb_tiles;
-        tb_tiles += s.tb_ntiles;
-        b->h_slots[n++] = s;
+        const BSlot& s = b->slot[id];
+        b->h_slots[n] = s;
+        const int count[LISTS] = {s.ntiles, s.tb_ntiles, s.rb_ntiles};
+        for (int l = 0; l < LISTS; ++l) {
+            b->h_find[n].begin[l] = total[l];
+            total[l] += count[l];
+        }
+        b->h_find[n++].id = id;
     }
-    const int need = std::max(tiles, tb_tiles);
+    const int need = std::max(total[LIST_ONE], total[LIST_RED]);
     if (need > b->partial_cap) {
         // grow the partials (invalidates a captured step graph)
         GSCL_HIP(hipStreamSynchronize(c->stream));
@@ -555,8 +607,8 @@ static int upload_table(gscl_batch* b) {
         b->partial_cap = cap;
     }
     b->h_hdr->nslots = n;
-    b->h_hdr->total_tiles = tiles;
-    b->h_hdr->total_tb_tiles = tb_tiles;
+    for (int l = 0; l < LISTS; ++l) b->h_hdr->total[l] = total[l];
+    if (n) GSCL_HIP(hipMemcpyAsync(b->d_find, b->h_find, sizeof(BFind) * n, hipMemcpyHostToDevice, c->stream));
     if (n) GSCL_HIP(hipMemcpyAsync(b->d_slots, b->h_slots, sizeof(BSlot) * n, hipMemcpyHostToDevice, c->stream));
     GSCL_HIP(hipMemcpyAsync(b->d_hdr, b->h_hdr, sizeof(BHeader), hipMemcpyHostToDevice, c->stream));
     GSCL_HIP(hipEventRecord(b->upload_done, c->stream));
@@ -644,8 +696,8 @@ extern "C" int gscl_batch_admit(gscl_batch* b, gscl_grid* u, const gscl_grid* f,
     s.nty = (s.ny + BNW - 1) / BNW;
     s.ncz = (s.nz + s.cz - 1) / s.cz;
     s.ntiles = s.ntx * s.nty * s.ncz;
-    s.tb_czmin = rtb > 0 ? rtb : TB_CZMIN;
-    if (b->desc.sweeps_per_pass > 1) set_tb_tiles(s, b->desc.sweeps_per_pass, s.tb_czmin);
+    s.rule_cz = rtb;
+    if (b->desc.sweeps_per_pass > 1) set_tb_tiles(s, b->desc.sweeps_per_pass);
     b->slot[id] = s;
     b->used[id] = true;
     b->work_ptr[id] = mem;
@@ -676,13 +728,13 @@ static void launch_batch_tb(const gscl_batch* b, int kp, dim3 grid, dim3 blk, hi
                             double omega) {
     static_assert(gk::TB_KMAX == 4, "one instantiation per level count");
     if (kp == 2) {
-        hipLaunchKernelGGL((batch_tb<MODE, RED, 2>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+        hipLaunchKernelGGL((batch_tb<MODE, RED, 2>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                            b->d_partials, parity, omega);
     } else if (kp == 4) {
-        hipLaunchKernelGGL((batch_tb<MODE, RED, 4>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+        hipLaunchKernelGGL((batch_tb<MODE, RED, 4>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                            b->d_partials, parity, omega);
     } else if constexpr (MODE != MODE_RBGS_TB) {
-        hipLaunchKernelGGL((batch_tb<MODE, RED, 3>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+        hipLaunchKernelGGL((batch_tb<MODE, RED, 3>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                            b->d_partials, parity, omega);
     }
 }
@@ -695,21 +747,21 @@ static int enqueue_step(gscl_batch* b) {
     const dim3 grid(b->persist_blocks), blk(64 * BNW);
     const int ms = b->desc.max_slots;
     const int kp = b->desc.sweeps_per_pass;
-    // blocked passes: two 16-wave blocks per CU in FP32 and in FP64
-    // two-level passes, else one (the LDS rows of the levels)
-    const dim3 tgrid(b->desc.precision == GSCL_PREC_F64 && kp > 2 ? 256 : 512), tblk(64 * gk::TB_NW);
+    // blocked passes: as many 8-wave blocks as are resident together, two per
+    // CU in FP32, one in FP64
+    const dim3 tgrid(b->desc.precision == GSCL_PREC_F64 ? 256 : 512), tblk(64 * gk::TB_NW);
     if (b->desc.method == GSCL_BATCH_RBGS) {
         if (kp > 1) {
             for (int q = 0; q < 2 * S / kp; ++q)  // even count: the step ends in u
                 launch_batch_tb<MODE_RBGS_TB, false>(b, kp, tgrid, tblk, s, q & 1, 0.0);
         } else {
             for (int k = 0; k < 2 * S; ++k)
-                hipLaunchKernelGGL((batch_sweep<MODE_RBGS, false>), grid, blk, 0, s, b->d_slots, b->d_state,
+                hipLaunchKernelGGL((batch_sweep<MODE_RBGS, false>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state,
                                    b->d_hdr, b->d_partials, k & 1, 0.0);
         }
-        hipLaunchKernelGGL((batch_sweep<MODE_RESID, true>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+        hipLaunchKernelGGL((batch_sweep<MODE_RESID, true>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                            b->d_partials, 0, 0.0);
-        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_state, b->d_hdr, b->d_partials,
+        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr, b->d_partials,
                            rtol2, S, (long long)b->desc.max_sweeps, 0, 0);
     } else if (b->desc.precision == GSCL_PREC_F64 && kp > 1) {
         const int np = S / kp;  // even: the step ends in u
@@ -719,34 +771,34 @@ static int enqueue_step(gscl_batch* b) {
             else
                 launch_batch_tb<MODE_F64, true>(b, kp, tgrid, tblk, s, q & 1, b->desc.omega);
         }
-        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_state, b->d_hdr, b->d_partials,
+        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr, b->d_partials,
                            rtol2, S, (long long)b->desc.max_sweeps, 0, 1);
     } else if (b->desc.precision == GSCL_PREC_F64) {
         for (int k = 1; k <= S; ++k) {
             const int parity = (k - 1) & 1;
             if (k < S)
-                hipLaunchKernelGGL((batch_sweep<MODE_F64, false>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+                hipLaunchKernelGGL((batch_sweep<MODE_F64, false>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                                    b->d_partials, parity, b->desc.omega);
             else
-                hipLaunchKernelGGL((batch_sweep<MODE_F64, true>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+                hipLaunchKernelGGL((batch_sweep<MODE_F64, true>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                                    b->d_partials, parity, b->desc.omega);
         }
-        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_state, b->d_hdr, b->d_partials,
+        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr, b->d_partials,
                            rtol2, S, (long long)b->desc.max_sweeps, 0, 0);
     } else {
-        hipLaunchKernelGGL((batch_sweep<MODE_RESID, true>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+        hipLaunchKernelGGL((batch_sweep<MODE_RESID, true>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                            b->d_partials, 0, b->desc.omega);
-        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_state, b->d_hdr, b->d_partials,
+        hipLaunchKernelGGL(batch_finish, dim3(ms), dim3(256), 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr, b->d_partials,
                            rtol2, S, (long long)b->desc.max_sweeps, 1, 0);
         if (kp > 1) {
             for (int q = 0; q < S / kp; ++q)
                 launch_batch_tb<MODE_F32, false>(b, kp, tgrid, tblk, s, q & 1, b->desc.omega);
         } else {
             for (int k = 1; k <= S; ++k)
-                hipLaunchKernelGGL((batch_sweep<MODE_F32, false>), grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr,
+                hipLaunchKernelGGL((batch_sweep<MODE_F32, false>), grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr,
                                    b->d_partials, (k - 1) & 1, b->desc.omega);
         }
-        hipLaunchKernelGGL(batch_update, grid, blk, 0, s, b->d_slots, b->d_state, b->d_hdr);
+        hipLaunchKernelGGL(batch_update, grid, blk, 0, s, b->d_slots, b->d_find, b->d_state, b->d_hdr);
     }
     GSCL_HIP(hipGetLastError());
     return GSCL_OK;
@@ -866,10 +918,12 @@ extern "C" int gscl_batch_destroy(gscl_batch* b) {
     hipEventDestroy(b->upload_done);
     hipFree(b->arena_mem);
     hipFree(b->d_slots);
+    hipFree(b->d_find);
     hipFree(b->d_state);
     hipFree(b->d_hdr);
     hipFree(b->d_partials);
     hipHostFree(b->h_slots);
+    hipHostFree(b->h_find);
     hipHostFree(b->h_state);
     hipHostFree(b->h_hdr);
     for (int k = 0; k < 2; ++k) {

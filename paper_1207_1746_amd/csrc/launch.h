@@ -8,6 +8,7 @@
 
 #include "kcommon.h"
 #include "tiled.h"
+#include "tb7.h"
 
 namespace gk {
 
@@ -78,12 +79,10 @@ hipError_t launch_diamond(DiamondArgs& a, int dtype, int kind, hipStream_t s);
 
 // Weighted Jacobi, k sweeps per pass (temporal blocking), 3D, F64 (dtype 0)
 // or F32 (dtype 1), Dirichlet or periodic; k in 1..TB_KMAX.
-struct TBArgs;
-constexpr int TB_KMAX = 4;
 hipError_t launch_wjacobi_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
 // k red-black colour passes per pass (first colour in a.p[3]), Dirichlet rule only.
 hipError_t launch_rbgs_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
-int tb_blocks(const Geo& g, int k, int cz);
+int64_t tb_blocks(const Geo& g, int k, int cz);
 
 // Generic linear operator (any offsets, per-grid boundary rule).  The terms are
 // ordered by output (the caller's order within one); tend[o] ends output o's.

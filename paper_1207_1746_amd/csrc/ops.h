@@ -14,6 +14,15 @@ namespace gk {
 
 enum { RV_OUT0 = 0, RV_UPDATE = 1, RV_RESIDUAL = 2 };
 
+// The value a relaxation gives a point: u its old value, s the sum of its
+// neighbours, inv one over their number.
+template <class T>
+__device__ __forceinline__ T relax_point(T u, T s, T fv, T omega, T h2, T inv) {
+#pragma clang fp contract(off)
+    const T avg = (s - h2 * fv) * inv;
+    return (T(1) - omega) * u + omega * avg;
+}
+
 // Weighted Jacobi on the constant-coefficient Laplacian (Section 5.2 averaging
 // with a source term): u' = (1-w) u + w (S - h^2 f) / (2 ndim).
 //   p[0] = omega, p[1] = h^2, p[2] = 1/h^2.
@@ -38,8 +47,7 @@ struct OpWJacobi {
         const T fv = HAS_F ? av[0] : T(0);
         const T omega = (T)p[0], h2 = (T)p[1], ih2 = (T)p[2];
         const T inv = T(1) / T(2 * NDIM);
-        const T avg = (s - h2 * fv) * inv;
-        const T un = (T(1) - omega) * u + omega * avg;
+        const T un = relax_point(u, s, fv, omega, h2, inv);
         o[0] = un;
         if (operand == RV_RESIDUAL)
             rv[0] = (double)(fv - (s - T(2 * NDIM) * u) * ih2);
@@ -75,8 +83,7 @@ struct OpRBGS {
         s = s + st.zm[0][0];
         const T fv = HAS_F ? av[0] : T(0);
         const T omega = (T)p[0], h2 = (T)p[1], ih2 = (T)p[2];
-        const T avg = (s - h2 * fv) * (T(1) / T(6));
-        const T un = (T(1) - omega) * u + omega * avg;
+        const T un = relax_point(u, s, fv, omega, h2, T(1) / T(6));
         const bool mine = ((st.ix + st.iy + st.iz) & 1) == (int)p[3];
         o[0] = mine ? un : u;
         double r;

@@ -2,22 +2,27 @@
 // relaxation: k sweeps (or k colour passes) per pass over HBM (wide ghost
 // zones).
 //
-// A block of 16 waves owns a working region of 64 columns x 32 rows (two rows
-// per wave) and marches it through z.  The region is the output tile grown
-// by k cells on every side: level t (the grid after t sweeps) is needed on
-// the tile grown by k - t cells, so after k levels the inner
-// (64 - 2k) x (32 - 2k) points are exact and are the only ones written.
+// A block of 8 waves owns a working region of 64 columns x 32 rows and marches
+// it through z.  Half a wave holds two rows of the region, each lane two
+// adjacent columns of both (an even x and the next), so the x neighbours
+// inside a pair are in the lane and the others one wave-wide DPP shift away
+// (a shift across the halves only fills ghost columns), the y neighbour inside
+// the two rows is in the lane, and only the row of the next half-wave up or
+// down goes through LDS.  The region is the output tile grown by k cells on
+// every side (columns: k rounded up to even): level t (the grid after t
+// sweeps) is needed on the tile grown by k - t cells, so after k levels the
+// inner points are exact and are the only ones written.
 //
-// At march step s the block loads input plane s (level 0) and computes, for
+// At march step s the block holds input plane s (level 0) and computes, for
 // t = 1..k, level t at plane s - t: its z neighbours are the thread's own
 // level t-1 values at planes s-t-1, s-t (registers) and s-t+1 (computed
-// earlier in the same step).  A wave holds whole rows (one column per lane),
-// so x neighbours come from the adjacent lanes by wave-wide DPP shifts and
-// the y neighbour inside the wave's own rows from a register; only the row
-// of the next wave up or down goes through LDS, where every wave stages its
-// level t-1 rows at the start of the step.  Each thread therefore holds two
-// planes per level plus the right-hand side of the k planes in flight, and
-// every input plane is read from HBM once per k sweeps.
+// earlier in the same step); every lane stages its level t-1 rows for the
+// half-waves above and below at the start of the step.  Every input plane is
+// read from HBM once per k sweeps.  Level t is first needed at plane
+// z0 - (k - t), which it reaches in step z0 - k + 2t; earlier steps leave it
+// out, so a chunk of cz planes costs k cz + k (k - 1) level steps.  Steps are
+// written out in groups of the period of the register windows, which makes
+// their shifts renamings.
 //
 // Outside the domain, levels take the Dirichlet value; under the periodic
 // rule the loads wrap and the computed values are the periodic extension.
@@ -27,11 +32,21 @@
 // Red-black levels (RB): level t is one colour pass of level t-1, colour
 // (c0 + t - 1) mod 2 with c0 = p[3], using the in-place pass's operator.  An
 // in-place colour pass reads only points of the other colour, which it does
-// not change, so it equals the same pass computed out of place; k levels are
-// therefore k in-place passes, bit for bit, and a pass of 2m levels is m
-// full red-black sweeps.
+// not change, so k levels are k in-place passes, bit for bit, and a pass of 2m
+// levels is m full red-black sweeps.  Here a level updates its colour in place
+// in the registers of its plane: of a lane's pair in a row exactly one point
+// has the colour, the same one at every level of a step, and it alternates
+// from row to row and from step to step; so the march starts on a step of
+// fixed parity and the point is known at compile time.  Half the points of a
+// level are computed, staged and shifted.
+//
+// Bound: Jacobi by the issue of vector instructions (FP32 and FP64 alike 4
+// cycles per wave; 200 and 250 per wave and step of 4 levels, 60-70% of the
+// time of a step) and the LDS rows; red-black by the two together with the
+// loads of a step (134 instructions, 46%).  Figures beside tb_pick_chunk.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ops.h"
@@ -51,31 +66,58 @@ struct TBArgs {
     RedArgs ra;
 };
 
-constexpr int TB_NW = 16, TB_RPW = 2, TB_ROWS = TB_NW * TB_RPW;
+constexpr int TB_KMAX = 4;  // most levels of a pass
+constexpr int TB_NW = 8, TB_RPL = 2, TB_COLS = 64, TB_ROWS = 4 * TB_NW;
 
-// Waves per SIMD that a K-level kernel is compiled for: two 16-wave blocks
-// per CU where two blocks' LDS rows (4096 K sizeof(T) bytes each) fit in the
-// 160 KB, else one; the register budget follows (64 or 128 VGPRs).  The
-// variants with a fused reduction at K = 2 in FP64, and with a fused
-// reduction and red-black levels at K = 4 in FP32, do not fit 64 VGPRs and
-// take one block.
-template <class T, int K, bool RED, bool RB>
+// Output tile of a k-level block: ghost columns are whole pairs.
+__host__ __device__ constexpr int tb_ghost_x(int k) { return (k + 1) & ~1; }
+__host__ __device__ constexpr int tb_out_x(int k) { return TB_COLS - 2 * tb_ghost_x(k); }
+__host__ __device__ constexpr int tb_out_y(int k) { return TB_ROWS - 2 * k; }
+
+// Waves per SIMD that a K-level kernel is compiled for: two blocks per CU
+// (128 VGPRs) where the LDS rows of two fit the 160 KB and the windows the
+// registers, else one (256).  (Spilled windows are worse than one block less:
+// their reloads wait for every load in flight.  Red-black, FP64, K = 4, 192^3:
+// 35 us per pass with 181 VGPRs, 48 with 128 and 40 spilled.)
+template <class T, int K, bool RB>
 constexpr int tb_waves_per_eu() {
-    if (RED && (sizeof(T) == 8 ? K == 2 : K == 4 && RB)) return 4;
-    return 2 * 4096 * K * (int)sizeof(T) + 1024 <= 160 * 1024 ? 8 : 4;
+    constexpr int lds = 2 * K * TB_RPL * 64 * TB_NW * (int)sizeof(T) * (RB ? 1 : 2);
+    return 2 * lds + 1024 <= 160 * 1024 && !(sizeof(T) == 8 && K >= 2) ? 4 : 2;
 }
 
-// Steps per written-out group of the z march: 2 (the period of the level
-// windows, so their shifts become register renamings rather than moves) for
-// the variants where that measured faster and fits the register budget
-// without spilling (FP64 at K = 3, and at K = 4 with 32-bit plane offsets
-// and not both a fused reduction and red-black levels; plain FP32 Jacobi
-// at K = 4), else 1.
-template <class T, int K, bool RED, bool RB, bool OFF32>
-constexpr int tb_unroll() {
-    if (sizeof(T) == 8) return K == 3 || (K == 4 && OFF32 && !(RED && RB)) ? 2 : 1;
-    return K == 4 && !RED && !RB ? 2 : 1;
+// z chunk of a launch whose chunk no one has set: the blocks of all chunks
+// share 256 CUs, and a block's time is its planes plus its warm-up, which
+// counts as `lead` planes (FP64 6.5, FP32 5; red-black 11, whose steps are
+// shorter but load as much).  One block per CU and round; where two fit
+// (FP32), a round of two takes 1.6 times one.  tiles(cz) is the number of
+// blocks with chunks of cz planes.  Measured per pass of 4 levels with a
+// right-hand side, us at the chunk taken (before: 16-wave blocks, one column
+// per lane, power-of-two chunks):
+//           Jacobi FP64      Jacobi FP32      red-black FP64
+//    32^3   13.8 -> 10.2     10.7 ->  7.4     14.4 ->  7.7
+//    96^3   21.4 -> 15.7     19.2 -> 10.9     22.6 -> 11.7
+//   192^3   64.5 -> 49       42.6 -> 29.4     71.4 -> 35
+//   256^3   125  -> 123      69.3 -> 58       139  -> 106
+template <class Tiles>
+inline int tb_pick_chunk(int nz, int64_t max_blocks, bool rb, bool f64, int k, Tiles&& tiles) {
+    const double lead = (rb ? 11.0 : f64 ? 6.5 : 5.0) * k / TB_KMAX;
+    int best = 0;
+    double best_cost = 0.0;
+    for (int cz = 1; cz <= std::min(nz, 128); ++cz) {
+        const int64_t n = tiles(cz);
+        if (n > max_blocks) continue;
+        const double rounds = f64 ? (double)((n + 255) / 256) : 1.6 * (double)(n / 512) + (n % 512 == 0 ? 0.0 : n % 512 <= 256 ? 1.0 : 1.6);
+        const double cost = rounds * (cz + lead);
+        if (best == 0 || cost <= best_cost) {
+            best = cz;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
+
+// Planes requested ahead of the one being computed.
+constexpr int TB_LA = 2;
 
 // Value of the lane below (lane - 1) or above (lane + 1) in the wave, by
 // wave-wide DPP shifts (wave_shr:1 / wave_shl:1); lanes without a source get 0.
@@ -99,215 +141,325 @@ __device__ __forceinline__ T exact_mul(T a, T b) {
     return a * b;
 }
 
-// One output tile (index `tile` of a.ntx x a.nty x a.ncz): K levels over its
-// z chunk; with RED, the fused operand of level K is added to acc.  Every
-// thread of the 16-wave block calls it.  K is a template parameter, so the
-// level loop unrolls to straight-line code with no per-level branches.
-// OFF32: every plane offset of the grid, (nz - 1) pz, fits 32 bits, so the
-// march keeps its plane offsets in fewer scalar registers.
-template <class T, bool HAS_F, int K, bool RED, bool RB, bool OFF32,
-          int UNROLL = tb_unroll<T, K, RED, RB, OFF32>()>
-__device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double& acc) {
-    static_assert(UNROLL == 1 || UNROLL == 2, "steps per group");
-    using Off = typename std::conditional<OFF32, uint32_t, int64_t>::type;
-    using Op = typename std::conditional<RB, OpRBGS<T, HAS_F>, OpWJacobi<T, T, 3, HAS_F>>::type;
-    constexpr int R = TB_RPW;
-    // the rows every wave stages per level, in two copies alternating by
-    // step: a step's staging writes the copy the previous step did not read,
-    // so one barrier per step suffices (FP64 at K = 4: 128 KB, one block
-    // per CU)
-    __shared__ T lds[2][K][TB_NW][R][64];
+// this lane's bit of a wave mask
+__device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-    const Geo& g = a.g;
-    constexpr int k = K;
-    const int ox = 64 - 2 * k, oy = TB_ROWS - 2 * k;  // output tile
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // waves whose rows border this wave's (the block's edge waves read their
-    // own rows there: those rows lie in the ghost zone, never written)
-    const int wdn = w > 0 ? w - 1 : 0, wup = w < TB_NW - 1 ? w + 1 : TB_NW - 1;
-    const int xt = tile % a.ntx, rest = tile / a.ntx, yt = rest % a.nty, zc = rest / a.nty;
-    const int z0 = zc * a.cz, z1 = min(z0 + a.cz, g.nz);
-    const int x = xt * ox - k + lane;
-    const bool dir = g.bc == BC_DIRICHLET;
-    const bool x_in = (unsigned)x < (unsigned)g.nx;
-    const int xs = x_in ? x : wrap_idx(x, g.nx, dir ? BC_CLAMP : g.bc);
-    const bool x_out = lane >= k && lane < 64 - k && x_in;
-    const T bcv = (T)g.bcv;
+// (((((xp + xm) + yp) + ym) + zp) + zm), the order of the plain sweeps
+template <class T>
+__device__ __forceinline__ T near_sum(T xp, T xm, T yp, T ym, T zp, T zm) {
+#pragma clang fp contract(off)
+    T s = xp + xm;
+    s = s + yp;
+    s = s + ym;
+    s = s + zp;
+    return s + zm;
+}
 
-    int row[R], yg[R];
-    bool xy_in[R], y_out[R];
-    // byte offset of this thread's column within a plane: 32 bits (the
-    // launchers refuse planes of 4 GiB or more), so each access is a
-    // wave-uniform 64-bit plane address plus one 32-bit register
-    uint32_t roff[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        row[i] = w * R + i;
-        const int y = yt * oy - k + row[i];
-        yg[i] = y;
-        const bool y_in = (unsigned)y < (unsigned)g.ny;
-        const int ys = y_in ? y : wrap_idx(y, g.ny, dir ? BC_CLAMP : g.bc);
-        roff[i] = (uint32_t)(((int64_t)ys * g.py + xs) * (int64_t)sizeof(T));
-        xy_in[i] = y_in && x_in;
-        y_out[i] = row[i] >= k && row[i] < TB_ROWS - k && y_in;
-    }
-    const T* const ub = static_cast<const T*>(a.u);
-    const T* const fb = static_cast<const T*>(a.f);
-    T* const ob = static_cast<T*>(a.out);
-
-    // element offset of the plane read for z: lin (= z * pz) inside the
-    // grid, the wrapped (periodic) or clamped (Dirichlet) plane outside.
-    // Plane offsets are wave-uniform and computed once per step for both
-    // rows; the right-hand side of plane s reuses the offset of the input
-    // plane s loaded one step earlier.
-    auto plane_off = [&](int z, Off lin) __attribute__((always_inline)) -> Off {
-        if ((unsigned)z < (unsigned)g.nz) return lin;
-        return (Off)((int64_t)wrap_idx(z, g.nz, dir ? BC_CLAMP : g.bc) * g.pz);
-    };
-    // level-0 value of row i at plane z (plane offset off)
-    auto load_u = [&](int z, Off off, int i) __attribute__((always_inline)) -> T {
-        const T v = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(ub + off) + roff[i]);
-        return (dir && !((unsigned)z < (unsigned)g.nz && xy_in[i])) ? bcv : v;
-    };
+// What a block keeps of its tile while it marches (see tb7_tile).  SPLIT: the
+// wrap of an odd row length splits pairs (periodic rule).
+template <class T, bool HAS_F, int K, bool RED, bool RB, bool SPLIT>
+struct TBMarch {
+    static constexpr int R = TB_RPL, NL = 64 * TB_NW;
+    // period of the register windows, in steps: even (the parity of the LDS
+    // copies, of the two-plane windows and of the red-black points), and at
+    // least the planes a window spans, K + 4 (two of them being loaded)
+    static constexpr int PER = (K + 5) / 2 * 2;
+    static constexpr int NH = RB ? PER : 2 * K;  // planes held
     // Without a fused reduction the right-hand side is held as h^2 f, formed
     // once per loaded value instead of once per level, and the operator is
     // given h^2 = 1: the product it forms is then exact, so every level
     // rounds as the plain sweep does.  (A fused residual needs f itself.)
-    constexpr bool PRE_H2 = HAS_F && !RED;
-    const T h2 = (T)a.p[1];
-    auto load_f = [&](Off off, int i) __attribute__((always_inline)) -> T {
-        if (!HAS_F) return T(0);
-        const T f = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(fb + off) + roff[i]);
-        return PRE_H2 ? exact_mul(h2, f) : f;
-    };
+    static constexpr bool PRE_H2 = HAS_F && !RED;
+    using Lds = T[2][K][R][RB ? 1 : 2][NL];
 
-    // at the start of step s: hist[L][i][1] = level L at plane s-1-L (the
-    // previous step's value), hist[L][i][0] = level L at plane s-2-L;
-    // fq[t][i] = f at plane s-t once the step has shifted the queue
-    T hist[K][R][2];
-    T fq[K + 1][R];
-#pragma unroll
-    for (int L = 0; L < K; ++L)
-#pragma unroll
-        for (int i = 0; i < R; ++i) hist[L][i][0] = hist[L][i][1] = T(0);
-#pragma unroll
-    for (int t = 0; t <= K; ++t)
-#pragma unroll
-        for (int i = 0; i < R; ++i) fq[t][i] = T(0);
+    const TBArgs& a;
+    Lds& lds;
+    double& acc;
+    const T* ub;
+    const T* fb;
+    T* ob;
+    int z0, z1, s_end;
+    int l, idx, dn, up;          // lane of the half-wave; LDS slots of this lane and the half-waves below / above
+    uint32_t roff[R];            // byte offset of this lane's pair in a plane
+    int d1;                      // byte distance to the pair's second point (sizeof(T) unless a wrap splits it)
+    bool whole;                  // rows are whole pairs
+    bool dir;                    // Dirichlet rule
+    // lane masks (scalar registers): inside the grid in x and y (periodic
+    // rule: any); the pair's points are written
+    uint64_t keep[R][2], out0[R], out1[R];
+    T bcv, omega, h2;
+    // RB: plane p in slot p mod PER (by the step's phase); else level L's two
+    // newest planes in 2 L, 2 L + 1, and nu the two planes being loaded
+    T u[NH][R][2];
+    T nu[2][R][2];
+    T fq[PER][R][2];             // h^2 f (or f) of plane p in slot p mod PER
 
-    // the first step whose level-k output is needed is s = z0 + k; steps
-    // from z0 - k on fill the windows (values below that are never used).
-    // The next step's input rows are requested before the current step is
-    // computed.  (A two-step lookahead measured no faster, FP32 and FP64.)
-    const int s_begin = z0 - k, s_end = z1 + k;
-    // offset of plane s (set when its input row was loaded), the linear
-    // offset of plane s + 1, and that of the plane level K writes, s - K
-    // (32-bit offsets wrap below plane 0; they are used only once they
-    // have been advanced into the grid, where modular sums are exact)
-    Off off_cur = plane_off(s_begin, (Off)((int64_t)s_begin * g.pz));
-    Off lin_next = (Off)((int64_t)(s_begin + 1) * g.pz);
-    Off lin_st = (Off)((int64_t)(s_begin - k) * g.pz);
-    T nu[R], nf[R];
-    {
-        const Off off_f = plane_off(s_begin - 1, (Off)((int64_t)(s_begin - 1) * g.pz));
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            nu[i] = load_u(s_begin, off_cur, i);
-            nf[i] = load_f(off_f, i);
+    // Plane offsets (elements): the input's next plane is zn, kept wrapped
+    // under the periodic rule and clamped at use under Dirichlet's; the
+    // right-hand side follows one plane behind, at foff.
+    int zn;
+    int64_t foff;
+    __device__ __forceinline__ int64_t next_off() {
+        const int nz = a.g.nz;
+        const int zz = dir ? min(max(zn, 0), nz - 1) : zn;
+        ++zn;
+        if (!dir && zn == nz) zn = 0;
+        return (int64_t)zz * a.g.pz;
+    }
+    __device__ __forceinline__ void load_pair(const char* pl, int i, T (&v)[2]) const {
+        if (SPLIT) {
+            v[0] = *reinterpret_cast<const T*>(pl + roff[i]);
+            v[1] = *reinterpret_cast<const T*>(pl + (uint32_t)((int)roff[i] + d1));
+        } else {
+            const Vec<T, 2> q = *reinterpret_cast<const Vec<T, 2>*>(pl + roff[i]);
+            v[0] = q.v[0];
+            v[1] = q.v[1];
         }
     }
+    // Request the next plane of the input (PH: the phase of its step) and the
+    // plane before it of the right-hand side.
+    template <int PH, bool F>
+    __device__ __forceinline__ void load_next() {
+        const int64_t off = next_off();
+        const char* pu = reinterpret_cast<const char*>(ub + off);
+#pragma unroll
+        for (int i = 0; i < R; ++i) load_pair(pu, i, RB ? u[RB ? PH % PER : 0][i] : nu[PH & 1][i]);
+        if (HAS_F && F) {
+            const char* pf = reinterpret_cast<const char*>(fb + foff);
+#pragma unroll
+            for (int i = 0; i < R; ++i) load_pair(pf, i, fq[(PH + PER - 1) % PER][i]);
+        }
+        foff = off;
+    }
 
-    // The march runs in whole groups of UNROLL steps (1 or 2), written out
-    // by hand: the compiler does not unroll a loop with a barrier and a
-    // variable trip count by itself.  A step past s_end (at most one) only
-    // computes: its planes lie beyond z1 + k, so nothing is stored or
-    // reduced, and its loads are of wrapped or clamped planes inside the
-    // grid.  The LDS copy of a step alternates with the step's parity.
-    for (int s0 = s_begin; s0 < s_end; s0 += UNROLL)
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const int s = s0 + u;
-        T cur[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            cur[i] = nu[i];
-#pragma unroll
-            for (int t = K; t >= 2; --t) fq[t][i] = fq[t - 1][i];
-            fq[1][i] = nf[i];
-        }
+    // Step s; PH = step index mod PER.  WARM: a step of the first group, whose
+    // levels are not all needed.
+    template <int PH, bool WARM>
+    __device__ __forceinline__ void step(const int s) {
+        // slot of plane s - j
+        auto slot = [](int j) constexpr { return ((PH - j) % PER + PER) % PER; };
+        constexpr int par = PH & 1;
+        // plane s arrives: boundary values, and h^2 f of plane s - 1
+        T cur[R][2];  // Jacobi: level 0 of plane s
         {
-            const Off off_next = plane_off(s + 1, lin_next);
+            const bool z_in = !dir || ((unsigned)s < (unsigned)a.g.nz);
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                nu[i] = load_u(s + 1, off_next, i);
-                nf[i] = load_f(off_cur, i);
-            }
-            off_cur = off_next;
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    T& v = RB ? u[RB ? slot(0) : 0][i][e] : nu[par][i][e];
+                    cur[i][e] = v = lane_of(z_in ? keep[i][e] : 0) ? v : bcv;
+                    if (PRE_H2) fq[slot(1)][i][e] = exact_mul(h2, fq[slot(1)][i][e]);
+                }
         }
-        // stage level t-1 of plane s-t for every level t
-        T(*lb)[TB_NW][R][64] = lds[UNROLL == 2 ? u : (s - s_begin) & 1];
+        // request plane s + TB_LA of the input, the one before of the right-hand side
+        // (redefined each step: the 64-bit form of the offsets is then not kept
+        // in registers, and accesses take a scalar base and a 32-bit offset)
+#pragma unroll
+        for (int i = 0; i < R; ++i) asm volatile("" : "+v"(roff[i]));
+        load_next<PH + TB_LA, true>();
+        const int lv = WARM ? (s - (z0 - K)) >> 1 : K;  // levels needed so far
+        // stage level t-1 of plane s - t (RB: the points this step does not update)
+        auto& lb = lds[par];
 #pragma unroll
         for (int t = 1; t <= K; ++t)
+            if (!WARM || t <= lv) {
 #pragma unroll
-            for (int i = 0; i < R; ++i) lb[t - 1][w][i][lane] = hist[t - 1][i][1];
+                for (int i = 0; i < R; ++i) {
+                    if (RB) {
+                        lb[t - 1][i][0][idx] = u[RB ? slot(t) : 0][i][1 - ((i + PH) & 1)];
+                    } else {
+                        // (the points of a pair in two rows of the copy: no bank conflicts)
+                        lb[t - 1][i][0][idx] = u[RB ? 0 : 2 * (t - 1) + 1][i][0];
+                        lb[t - 1][i][RB ? 0 : 1][idx] = u[RB ? 0 : 2 * (t - 1) + 1][i][1];
+                    }
+                }
+            }
         __syncthreads();
-        // newest value of the level below, per row
-        T below[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) below[i] = cur[i];
+        const T inv = T(1) / T(6), h2l = PRE_H2 ? T(1) : h2;
 #pragma unroll
         for (int t = 1; t <= K; ++t) {
             const int zp = s - t;
-            const bool z_in = (unsigned)zp < (unsigned)g.nz;
-            // red-black: this level's colour in p[3]
-            const double pl[4] = {a.p[0], PRE_H2 ? 1.0 : a.p[1], a.p[2], (double)(((int)a.p[3] + t - 1) & 1)};
-            const double* pt = pl;
-            // level t-1 of plane s-t, this wave's rows
-            T cc[R];
+            const bool z_in = !dir || ((unsigned)zp < (unsigned)a.g.nz);
+            T c[R][2], val[R][2];
+            double rv[R][2];
+            if (!RB) {
 #pragma unroll
-            for (int i = 0; i < R; ++i) cc[i] = hist[t - 1][i][1];
+                for (int i = 0; i < R; ++i)
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                Star<T, 1, 1> st;
-                st.c[0] = cc[i];
-                st.zm[0][0] = hist[t - 1][i][0];
-                st.zp[0][0] = below[i];
-                st.xm[0][0] = lane_shift<DPP_WAVE_SHR1>(cc[i]);
-                st.xp[0][0] = lane_shift<DPP_WAVE_SHL1>(cc[i]);
-                st.ym[0][0] = i > 0 ? cc[i > 0 ? i - 1 : 0] : lb[t - 1][wdn][R - 1][lane];
-                st.yp[0][0] = i < R - 1 ? cc[i < R - 1 ? i + 1 : 0] : lb[t - 1][wup][0][lane];
-                st.ix = x;
-                st.iy = yg[i];
-                st.iz = zp;
-                T av[1] = {fq[t][i]}, bv[1] = {T(0)};
-                T o[1];
-                double rv[1];
-                Op::apply(st, av, bv, pt, o, rv, a.operand);
-                const bool inside = z_in && xy_in[i];
-                const T val = (dir && !inside) ? bcv : o[0];
-                if (t == k) {
-                    if (x_out && y_out[i] && zp >= z0 && zp < z1) {
-                        *reinterpret_cast<T*>(reinterpret_cast<char*>(ob + lin_st) + roff[i]) = val;
-                        if (RED) acc = red_acc(acc, rv[0], a.ra.op);
+                    for (int e = 0; e < 2; ++e) val[i][e] = c[i][e] = u[RB ? 0 : 2 * (t - 1) + 1][i][e];
+            }
+            if (!WARM || t <= lv) {
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        if (RB && e != ((i + PH) & 1)) continue;
+                        T old, sum;
+                        if (RB) {
+                            auto& q = u[RB ? slot(t) : 0];
+                            const T xs = q[i][1 - e];
+                            const T xm = e == 0 ? lane_shift<DPP_WAVE_SHR1>(xs) : xs;
+                            const T xp = e == 0 ? xs : lane_shift<DPP_WAVE_SHL1>(xs);
+                            const T ym = i > 0 ? q[0][e] : lb[t - 1][1][0][dn];
+                            const T yp = i > 0 ? lb[t - 1][0][0][up] : q[1][e];
+                            sum = near_sum(xp, xm, yp, ym, u[RB ? slot(t - 1) : 0][i][e], u[RB ? slot(t + 1) : 0][i][e]);
+                            old = q[i][e];
+                        } else {
+                            const T xm = e == 0 ? lane_shift<DPP_WAVE_SHR1>(c[i][1]) : c[i][0];
+                            const T xp = e == 0 ? c[i][1] : lane_shift<DPP_WAVE_SHL1>(c[i][0]);
+                            const T ym = i > 0 ? c[0][e] : lb[t - 1][1][RB ? 0 : e][dn];
+                            const T yp = i > 0 ? lb[t - 1][0][RB ? 0 : e][up] : c[1][e];
+                            sum = near_sum(xp, xm, yp, ym, cur[i][e], u[RB ? 0 : 2 * (t - 1)][i][e]);
+                            old = c[i][e];
+                        }
+                        const T fv = HAS_F ? fq[slot(t)][i][e] : T(0);
+                        const T un = relax_point(old, sum, fv, omega, h2l, inv);
+                        if (RED && t == K) {
+#pragma clang fp contract(off)
+                            if (a.operand == RV_RESIDUAL)
+                                rv[i][e] = (double)(fv - (sum - T(6) * old) * (T)a.p[2]);
+                            else
+                                rv[i][e] = a.operand == RV_UPDATE ? (double)(un - old) : (double)un;
+                        }
+                        if (RB)
+                            u[RB ? slot(t) : 0][i][e] = lane_of(z_in ? keep[i][e] : 0) ? un : old;
+                        else
+                            val[i][e] = lane_of(z_in ? keep[i][e] : 0) ? un : bcv;
+                    }
+            }
+            if (t == K && zp >= z0) {  // (zp < z1 always)
+                char* po = reinterpret_cast<char*>(ob + (int64_t)zp * a.g.pz);
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    Vec<T, 2> q;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        q.v[e] = RB ? u[RB ? slot(t) : 0][i][e] : val[i][e];
+                        // keep the computation out of the branches below
+                        asm volatile("" : "+v"(q.v[e]));
+                    }
+                    if (whole) {
+                        if (lane_of(out0[i])) *reinterpret_cast<Vec<T, 2>*>(po + roff[i]) = q;
+                    } else {
+                        if (lane_of(out0[i])) *reinterpret_cast<T*>(po + roff[i]) = q.v[0];
+                        if (lane_of(out1[i])) *reinterpret_cast<T*>(po + roff[i] + sizeof(T)) = q.v[1];
+                    }
+                    if (RED) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            if (RB && e != ((i + PH) & 1)) continue;
+                            if (lane_of(e == 0 ? out0[i] : out1[i])) acc = red_acc(acc, rv[i][e], a.ra.op);
+                        }
                     }
                 }
+            }
+            if (!RB) {
                 // shift the level t-1 window; the new level t value is the
-                // z+1 neighbour of level t+1 in this step
-                hist[t - 1][i][0] = hist[t - 1][i][1];
-                hist[t - 1][i][1] = below[i];
-                below[i] = val;
+                // z + 1 neighbour of level t + 1 in this step
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        u[RB ? 0 : 2 * (t - 1)][i][e] = c[i][e];
+                        u[RB ? 0 : 2 * (t - 1) + 1][i][e] = cur[i][e];
+                        cur[i][e] = val[i][e];
+                    }
             }
         }
-        lin_next += (Off)g.pz;
-        lin_st += (Off)g.pz;
+    }
+
+    // Steps PH .. PER - 1 of a group from step s on; true once s_end is reached.
+    template <int PH, bool WARM>
+    __device__ __forceinline__ bool group(int& s) {
+        step<PH, WARM>(s);
+        if (++s >= s_end) return true;
+        if constexpr (PH + 1 < PER) return group<PH + 1, WARM>(s);
+        return false;
+    }
+};
+
+// One output tile (index `tile` of a.ntx x a.nty x a.ncz): K levels over its
+// z chunk; with RED, the fused operand of level K is added to acc.  Every
+// thread of the block calls it.
+template <class T, bool HAS_F, int K, bool RED, bool RB, bool SPLIT = false>
+__device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double& acc) {
+    using M = TBMarch<T, HAS_F, K, RED, RB, SPLIT>;
+    // the rows every lane stages per level, in two copies alternating by
+    // step: a step's staging writes the copy the previous step did not read,
+    // so one barrier per step suffices
+    __shared__ typename M::Lds lds;
+    constexpr int R = TB_RPL, G = tb_ghost_x(K);
+    const Geo& g = a.g;
+    M m{a, lds, acc};
+    m.ub = static_cast<const T*>(a.u);
+    m.fb = static_cast<const T*>(a.f);
+    m.ob = static_cast<T*>(a.out);
+    const int xt = tile % a.ntx, rest = tile / a.ntx, yt = rest % a.nty, zc = rest / a.nty;
+    m.z0 = zc * a.cz;
+    m.z1 = min(m.z0 + a.cz, g.nz);
+    m.dir = g.bc == BC_DIRICHLET;
+    m.bcv = (T)g.bcv;
+    m.omega = (T)a.p[0];
+    m.h2 = (T)a.p[1];
+    const int rg = threadIdx.x >> 5;  // half-wave: rows 2 rg, 2 rg + 1 of the region
+    m.l = threadIdx.x & 31;
+    m.idx = threadIdx.x;
+    // (the region's edge rows read their own: they lie in the ghost zone)
+    m.dn = rg > 0 ? m.idx - 32 : m.idx;
+    m.up = rg < 2 * TB_NW - 1 ? m.idx + 32 : m.idx;
+    const int x = xt * tb_out_x(K) - G + 2 * m.l;  // even
+    const int rule = m.dir ? BC_CLAMP : g.bc;
+    m.whole = (g.nx & 1) == 0;
+    // x even: a pair inside the grid, or starting at its last column (the
+    // second point is then the row's padding, never used), is contiguous; a
+    // pair outside under the Dirichlet rule is read anywhere and replaced
+    const int xs = (unsigned)x < (unsigned)g.nx ? x : (m.dir ? (x < 0 ? 0 : (g.nx - 1) & ~1) : wrap_idx(x, g.nx, rule));
+    m.d1 = !SPLIT ? (int)sizeof(T) : (wrap_idx(x + 1, g.nx, rule) - xs) * (int)sizeof(T);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int row = rg * R + i, y = yt * tb_out_y(K) - K + row;
+        const bool y_in = (unsigned)y < (unsigned)g.ny;
+        const int ys = y_in ? y : wrap_idx(y, g.ny, rule);
+        m.roff[i] = (uint32_t)(((int64_t)ys * g.py + xs) * (int64_t)sizeof(T));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) m.keep[i][e] = __ballot(!m.dir || (y_in && (unsigned)(x + e) < (unsigned)g.nx));
+        const bool out = row >= K && row < TB_ROWS - K && y_in && m.l >= G / 2 && m.l < (TB_COLS - G) / 2 && x < g.nx;
+        m.out0[i] = __ballot(out);
+        m.out1[i] = __ballot(out && x + 1 < g.nx);
+    }
+#pragma unroll
+    for (int j = 0; j < M::NH; ++j)
+#pragma unroll
+        for (int i = 0; i < R; ++i) m.u[j][i][0] = m.u[j][i][1] = T(0);
+#pragma unroll
+    for (int j = 0; j < M::PER; ++j)
+#pragma unroll
+        for (int i = 0; i < R; ++i) m.fq[j][i][0] = m.fq[j][i][1] = T(0);
+
+    // Level K is first needed at plane z0 in step z0 + K; steps from z0 - K on
+    // fill the windows.  RB: the point (x + e, y, s - t) of row i has colour
+    // (e + i + K + s - t) mod 2 (x is even, y = i + K mod 2) and level t updates
+    // colour (c0 + t - 1) mod 2, so the point of step s is
+    // e = (i + K + s + c0 + 1) mod 2: start where that is i mod 2.
+    int s = m.z0 - K;
+    if (RB && ((s + K + (int)a.p[3] + 1) & 1)) --s;
+    m.s_end = m.z1 + K;
+    m.zn = m.dir ? s : wrap_idx(s, g.nz, BC_PERIODIC);
+    m.template load_next<0, false>();
+    m.template load_next<1, true>();
+    static_assert(TB_LA == 2, "planes requested before the march");
+    // (a group is at least 2 K steps)
+    if (m.template group<0, true>(s)) return;
+    while (!m.template group<0, false>(s)) {
     }
 }
 
-template <class T, bool HAS_F, int K, bool RED, bool RB, bool OFF32>
-__global__ __launch_bounds__(64 * TB_NW, (tb_waves_per_eu<T, K, RED, RB>())) void tb7_sweep(TBArgs a) {
+template <class T, bool HAS_F, int K, bool RED, bool RB, bool SPLIT>
+__global__ __launch_bounds__(64 * TB_NW, (tb_waves_per_eu<T, K, RB>())) void tb7_sweep(TBArgs a) {
     const int tile = xcd_remap(blockIdx.x, a.ntx * a.nty * a.ncz);
     double acc = 0.0;
-    tb7_tile<T, HAS_F, K, RED, RB, OFF32>(a, tile, acc);
+    tb7_tile<T, HAS_F, K, RED, RB, SPLIT>(a, tile, acc);
     if (RED) block_reduce(acc, a.ra, tile);
 }
 
