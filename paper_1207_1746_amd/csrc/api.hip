@@ -438,25 +438,27 @@ static int take_partials(gscl_ctx* c, const FixedScratch* fx, int64_t nblocks) {
 // been held against, that of nominal chunks of tiles with exactly k ghost
 // columns.
 static int tb_chunk(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d, const gk::Geo& g, int k) {
+    const bool rb = kind == GSCL_K_RBGS_TB, pairs = gk::tb_pairs(dtype == GSCL_F64, rb);
     const int nominal = pick_tile(c, kind, dtype, d).cz;
     if (c->tiles.count(std::make_tuple(kind, dtype, d.n[0], d.n[1], d.n[2]))) return nominal;
-    const int64_t most = std::max<int64_t>(gk::tb_blocks(g, k, nominal), 2048);
-    const int cz = gk::tb_pick_chunk(g.nz, most, kind == GSCL_K_RBGS_TB, dtype == GSCL_F64, k,
-                                     [&](int q) { return gk::tb_blocks(g, k, q); });
+    const int64_t most = std::max<int64_t>(gk::tb_blocks(g, k, nominal, pairs), 2048);
+    const int cz = gk::tb_pick_chunk(g.nz, most, rb, dtype == GSCL_F64, k,
+                                     [&](int q) { return gk::tb_blocks(g, k, q, pairs); });
     return cz ? cz : nominal;
 }
 
 static int tb_partials(gscl_ctx* c, const FixedScratch* fx, int kind, int dtype, const gscl_grid_desc& d,
                        const gk::Geo& g, int k, int& cz) {
+    const bool pairs = gk::tb_pairs(dtype == GSCL_F64, kind == GSCL_K_RBGS_TB);
     if (fx) {
         const int nominal = pick_tile(c, kind, dtype, d).cz, ox = gk::TB_COLS - 2 * k, oy = gk::TB_ROWS - 2 * k;
         const int rc = take_partials(c, fx, (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) *
                                                 ((g.nz + nominal - 1) / nominal));
         if (rc) return rc;
-        while (gk::tb_blocks(g, k, cz) > GSCL_NOALLOC_PARTIALS) ++cz;  // (a few tiles more at odd k)
+        while (gk::tb_blocks(g, k, cz, pairs) > GSCL_NOALLOC_PARTIALS) ++cz;  // (a few tiles more at odd k)
         return GSCL_OK;
     }
-    return take_partials(c, fx, gk::tb_blocks(g, k, cz));
+    return take_partials(c, fx, gk::tb_blocks(g, k, cz, pairs));
 }
 
 static void fill_red(gscl_ctx* c, const gscl_reduce_desc* rd, gk::RedArgs& ra, const FixedScratch* fx = nullptr) {

@@ -189,7 +189,7 @@ template <int MODE>
 using BatchT = typename std::conditional<MODE == MODE_F32, float, double>::type;
 
 template <int MODE, bool RED, int K>
-__global__ __launch_bounds__(64 * gk::TB_NW, (gk::tb_waves_per_eu<BatchT<MODE>, K, MODE == MODE_RBGS_TB>()))
+__global__ __launch_bounds__(64 * gk::tb_waves(gk::tb_pairs(sizeof(BatchT<MODE>) == 8, MODE == MODE_RBGS_TB)), (gk::tb_waves_per_eu<BatchT<MODE>, K, MODE == MODE_RBGS_TB>()))
 void batch_tb(const BSlot* __restrict__ slots, const BFind* __restrict__ find, const BState* st, const BHeader* hdr,
               double* partials, int parity, double omega) {
     using T = BatchT<MODE>;
@@ -524,6 +524,9 @@ static bool batch_ok(const gscl_batch* b) { return b && b->magic == BATCH_MAGIC;
 
 // Rebuild the compact table (admitted slots in id order, tile prefix sums) and
 // upload it on the context stream.
+static bool tb_pairs_of(const gscl_batch_desc& d) {
+    return gk::tb_pairs(d.precision == GSCL_PREC_F64, d.method == GSCL_BATCH_RBGS);
+}
 static int tb_cols(const BSlot& s) { return s.tntx * s.tnty; }
 static int chunk_of(const BSlot& s, int cz) { return std::max(1, std::min(cz, s.nz)); }
 
@@ -531,8 +534,8 @@ static int chunk_of(const BSlot& s, int cz) { return std::max(1, std::min(cz, s.
 // own extents (and the batch's rule), so its result is the same among any
 // others.  The z chunk is a power of two up to tiles per plane * nz / 160, but
 // at least 16 planes: the slots of a batch fill the chip together.
-static void set_tb_tiles(BSlot& s, int kp) {
-    s.tntx = (s.nx + gk::tb_out_x(kp) - 1) / gk::tb_out_x(kp);
+static void set_tb_tiles(BSlot& s, int kp, bool pairs) {
+    s.tntx = (s.nx + gk::tb_out_x(kp, pairs) - 1) / gk::tb_out_x(kp, pairs);
     s.tnty = (s.ny + gk::tb_out_y(kp) - 1) / gk::tb_out_y(kp);
     const int64_t want = std::max<int64_t>(1, (int64_t)tb_cols(s) * s.nz / 160);
     int cz = s.rule_cz > 0 ? s.rule_cz : 16;
@@ -697,7 +700,7 @@ extern "C" int gscl_batch_admit(gscl_batch* b, gscl_grid* u, const gscl_grid* f,
     s.ncz = (s.nz + s.cz - 1) / s.cz;
     s.ntiles = s.ntx * s.nty * s.ncz;
     s.rule_cz = rtb;
-    if (b->desc.sweeps_per_pass > 1) set_tb_tiles(s, b->desc.sweeps_per_pass);
+    if (b->desc.sweeps_per_pass > 1) set_tb_tiles(s, b->desc.sweeps_per_pass, tb_pairs_of(b->desc));
     b->slot[id] = s;
     b->used[id] = true;
     b->work_ptr[id] = mem;
@@ -747,9 +750,9 @@ static int enqueue_step(gscl_batch* b) {
     const dim3 grid(b->persist_blocks), blk(64 * BNW);
     const int ms = b->desc.max_slots;
     const int kp = b->desc.sweeps_per_pass;
-    // blocked passes: as many 8-wave blocks as are resident together, two per
-    // CU in FP32, one in FP64
-    const dim3 tgrid(b->desc.precision == GSCL_PREC_F64 ? 256 : 512), tblk(64 * gk::TB_NW);
+    // blocked passes: as many blocks as are resident together, two per CU in
+    // FP32, one in FP64
+    const dim3 tgrid(b->desc.precision == GSCL_PREC_F64 ? 256 : 512), tblk(64 * gk::tb_waves(tb_pairs_of(b->desc)));
     if (b->desc.method == GSCL_BATCH_RBGS) {
         if (kp > 1) {
             for (int q = 0; q < 2 * S / kp; ++q)  // even count: the step ends in u

@@ -5,31 +5,33 @@
 
 namespace gk {
 
-int64_t tb_blocks(const Geo& g, int k, int cz) {
-    const int ox = tb_out_x(k), oy = tb_out_y(k);
+int64_t tb_blocks(const Geo& g, int k, int cz, bool pairs) {
+    const int ox = tb_out_x(k, pairs), oy = tb_out_y(k);
     return (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) * ((g.nz + cz - 1) / cz);
 }
 
 template <class T, bool HAS_F, int K, bool RB>
 static hipError_t run_tb(TBArgs& a, bool red, hipStream_t s, int* nblocks) {
-    const int n = (int)tb_blocks(a.g, K, a.cz);
-    a.ntx = (a.g.nx + tb_out_x(K) - 1) / tb_out_x(K);
+    const int n = (int)tb_blocks(a.g, K, a.cz, tb_pairs(sizeof(T) == 8, RB));
+    constexpr int OX = tb_out_x(K, tb_pairs(sizeof(T) == 8, RB));
+    a.ntx = (a.g.nx + OX - 1) / OX;
     a.nty = (a.g.ny + tb_out_y(K) - 1) / tb_out_y(K);
     a.ncz = (a.g.nz + a.cz - 1) / a.cz;
     *nblocks = n;
     if (n == 0) return hipSuccess;
     // the wrap of an odd row length splits pairs of columns
-    bool split = false;
-    if constexpr (!RB) split = a.g.bc == BC_PERIODIC && (a.g.nx & 1);
+    constexpr bool PAIRS = tb_pairs(sizeof(T) == 8, RB), CAN_SPLIT = PAIRS && !RB;
+    const bool split = CAN_SPLIT && a.g.bc == BC_PERIODIC && (a.g.nx & 1);
+    const dim3 blk(64 * tb_waves(PAIRS));
     if (red) {
-        if (split) hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, true, RB, !RB>), dim3(n), dim3(64 * TB_NW), 0, s, a);
-        else hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, true, RB, false>), dim3(n), dim3(64 * TB_NW), 0, s, a);
+        if (split) hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, true, RB, CAN_SPLIT>), dim3(n), blk, 0, s, a);
+        else hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, true, RB, false>), dim3(n), blk, 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_reduce_finish(a.ra, n, s);
     }
-    if (split) hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, false, RB, !RB>), dim3(n), dim3(64 * TB_NW), 0, s, a);
-    else hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, false, RB, false>), dim3(n), dim3(64 * TB_NW), 0, s, a);
+    if (split) hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, false, RB, CAN_SPLIT>), dim3(n), blk, 0, s, a);
+    else hipLaunchKernelGGL((tb7_sweep<T, HAS_F, K, false, RB, false>), dim3(n), blk, 0, s, a);
     return hipGetLastError();
 }
 

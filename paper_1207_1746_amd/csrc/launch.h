@@ -82,7 +82,7 @@ hipError_t launch_diamond(DiamondArgs& a, int dtype, int kind, hipStream_t s);
 hipError_t launch_wjacobi_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
 // k red-black colour passes per pass (first colour in a.p[3]), Dirichlet rule only.
 hipError_t launch_rbgs_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
-int64_t tb_blocks(const Geo& g, int k, int cz);
+int64_t tb_blocks(const Geo& g, int k, int cz, bool pairs);
 
 // Generic linear operator (any offsets, per-grid boundary rule).  The terms are
 // ordered by output (the caller's order within one); tend[o] ends output o's.
@@ -133,4 +133,6 @@ namespace gk {
 // Poisson residual r = f - Lap_h x (F64 math, F32 output) with optional fused
 // sum of squares of r.
 hipError_t launch_poisson_resid(TArgs& a, const TileCfg& c, bool red, hipStream_t s, int* nblocks);
+// Its fused reduction alone: no output grid.
+hipError_t launch_poisson_norm(TArgs& a, const TileCfg& c, hipStream_t s, int* nblocks);
 }  // namespace gk

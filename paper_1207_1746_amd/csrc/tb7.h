@@ -2,16 +2,20 @@
 // relaxation: k sweeps (or k colour passes) per pass over HBM (wide ghost
 // zones).
 //
-// A block of 8 waves owns a working region of 64 columns x 32 rows and marches
-// it through z.  Half a wave holds two rows of the region, each lane two
-// adjacent columns of both (an even x and the next), so the x neighbours
-// inside a pair are in the lane and the others one wave-wide DPP shift away
-// (a shift across the halves only fills ghost columns), the y neighbour inside
-// the two rows is in the lane, and only the row of the next half-wave up or
-// down goes through LDS.  The region is the output tile grown by k cells on
-// every side (columns: k rounded up to even): level t (the grid after t
-// sweeps) is needed on the tile grown by k - t cells, so after k levels the
-// inner points are exact and are the only ones written.
+// A block owns a working region of 64 columns x 32 rows and marches it through
+// z; a group of lanes holds two rows of it.  FP64 Jacobi: the group is a wave,
+// each lane one column; the x neighbours are a wave-wide DPP shift away.
+// Otherwise ("pairs") the group is half a wave, each lane two adjacent columns
+// (an even x and the next); the x neighbours inside a pair are in the lane, the
+// others a shift away (a shift across the halves only fills ghost columns): half
+// the shifts, but twice the registers per lane, which in FP64 leave Jacobi two
+// waves per SIMD (1.5 us a step of 4 levels; four rows of one column 1.47; 16
+// waves of two rows 1.35).  The y neighbour inside the two rows is in the lane,
+// and only the row of the next group up or down goes through LDS.  The region is
+// the output tile grown by k cells on every side (pairs: columns by k rounded up
+// to even): level t (the grid after t sweeps) is needed on the tile grown by
+// k - t cells, so after k levels the inner points are exact and are the only
+// ones written.
 //
 // At march step s the block holds input plane s (level 0) and computes, for
 // t = 1..k, level t at plane s - t: its z neighbours are the thread's own
@@ -40,10 +44,10 @@
 // fixed parity and the point is known at compile time.  Half the points of a
 // level are computed, staged and shifted.
 //
-// Bound: Jacobi by the issue of vector instructions (FP32 and FP64 alike 4
-// cycles per wave; 200 and 250 per wave and step of 4 levels, 60-70% of the
-// time of a step) and the LDS rows; red-black by the two together with the
-// loads of a step (134 instructions, 46%).  Figures beside tb_pick_chunk.
+// Bound: the issue of vector instructions (FP32 and FP64 alike 4 cycles per
+// wave; per block and step of 4 levels 1600 in FP32, 2300 in FP64, 1070
+// red-black, 45-70% of the time of a step) and the LDS rows, which the barrier
+// keeps from overlapping much.  Figures beside tb_pick_chunk.
 #pragma once
 
 #include <algorithm>
@@ -67,22 +71,26 @@ struct TBArgs {
 };
 
 constexpr int TB_KMAX = 4;  // most levels of a pass
-constexpr int TB_NW = 8, TB_RPL = 2, TB_COLS = 64, TB_ROWS = 4 * TB_NW;
+constexpr int TB_COLS = 64, TB_ROWS = 32;
 
-// Output tile of a k-level block: ghost columns are whole pairs.
-__host__ __device__ constexpr int tb_ghost_x(int k) { return (k + 1) & ~1; }
-__host__ __device__ constexpr int tb_out_x(int k) { return TB_COLS - 2 * tb_ghost_x(k); }
+// Whether a kernel's lanes hold pairs of columns, and its waves.
+constexpr bool tb_pairs(bool f64, bool rb) { return rb || !f64; }
+constexpr int tb_waves(bool pairs) { return pairs ? 8 : 16; }
+
+// Output tile of a k-level block (pairs: ghost columns are whole pairs).
+__host__ __device__ constexpr int tb_ghost_x(int k, bool pairs) { return pairs ? (k + 1) & ~1 : k; }
+__host__ __device__ constexpr int tb_out_x(int k, bool pairs) { return TB_COLS - 2 * tb_ghost_x(k, pairs); }
 __host__ __device__ constexpr int tb_out_y(int k) { return TB_ROWS - 2 * k; }
 
 // Waves per SIMD that a K-level kernel is compiled for: two blocks per CU
-// (128 VGPRs) where the LDS rows of two fit the 160 KB and the windows the
-// registers, else one (256).  (Spilled windows are worse than one block less:
+// (8 waves: 128 VGPRs) where the LDS rows of two fit the 160 KB and the windows
+// the registers, else one (8 waves: 256, 16: 128).  (Spilled windows are worse than one block less:
 // their reloads wait for every load in flight.  Red-black, FP64, K = 4, 192^3:
 // 35 us per pass with 181 VGPRs, 48 with 128 and 40 spilled.)
 template <class T, int K, bool RB>
 constexpr int tb_waves_per_eu() {
-    constexpr int lds = 2 * K * TB_RPL * 64 * TB_NW * (int)sizeof(T) * (RB ? 1 : 2);
-    return 2 * lds + 1024 <= 160 * 1024 && !(sizeof(T) == 8 && K >= 2) ? 4 : 2;
+    if (!tb_pairs(sizeof(T) == 8, RB)) return 4;
+    return sizeof(T) == 4 || K == 1 ? 4 : 2;
 }
 
 // z chunk of a launch whose chunk no one has set: the blocks of all chunks
@@ -94,10 +102,10 @@ constexpr int tb_waves_per_eu() {
 // right-hand side, us at the chunk taken (before: 16-wave blocks, one column
 // per lane, power-of-two chunks):
 //           Jacobi FP64      Jacobi FP32      red-black FP64
-//    32^3   13.8 -> 10.2     10.7 ->  7.4     14.4 ->  7.7
-//    96^3   21.4 -> 15.7     19.2 -> 10.9     22.6 -> 11.7
-//   192^3   64.5 -> 49       42.6 -> 29.4     71.4 -> 35
-//   256^3   125  -> 123      69.3 -> 58       139  -> 106
+//    32^3   13.8 -> 10.6     10.7 ->  7.8     14.4 ->  7.7
+//    96^3   21.4 -> 15.6     19.2 -> 11.1     22.6 -> 11.7
+//   192^3   64.5 -> 45       42.6 -> 29.0     71.4 -> 35
+//   256^3   117  -> 113      69.3 -> 57       139  -> 106
 template <class Tiles>
 inline int tb_pick_chunk(int nz, int64_t max_blocks, bool rb, bool f64, int k, Tiles&& tiles) {
     const double lead = (rb ? 11.0 : f64 ? 6.5 : 5.0) * k / TB_KMAX;
@@ -115,9 +123,6 @@ inline int tb_pick_chunk(int nz, int64_t max_blocks, bool rb, bool f64, int k, T
     }
     return best;
 }
-
-// Planes requested ahead of the one being computed.
-constexpr int TB_LA = 2;
 
 // Value of the lane below (lane - 1) or above (lane + 1) in the wave, by
 // wave-wide DPP shifts (wave_shr:1 / wave_shl:1); lanes without a source get 0.
@@ -155,22 +160,29 @@ __device__ __forceinline__ T near_sum(T xp, T xm, T yp, T ym, T zp, T zm) {
     return s + zm;
 }
 
-// What a block keeps of its tile while it marches (see tb7_tile).  SPLIT: the
-// wrap of an odd row length splits pairs (periodic rule).
+// What a block keeps of its tile while it marches (see tb7_tile).
+// SPLIT: the wrap of an odd row length splits pairs (periodic rule).
 template <class T, bool HAS_F, int K, bool RED, bool RB, bool SPLIT>
 struct TBMarch {
-    static constexpr int R = TB_RPL, NL = 64 * TB_NW;
+    static constexpr bool PAIRS = tb_pairs(sizeof(T) == 8, RB);
+    // rows and columns of a lane, lanes of a group and of a block
+    static constexpr int R = 2, NV = PAIRS ? 2 : 1, GROUP = PAIRS ? 32 : 64, NL = 64 * tb_waves(PAIRS);
+    // values staged per row: red-black only those of one colour
+    static constexpr int NE = RB ? 1 : NV;
     // period of the register windows, in steps: even (the parity of the LDS
     // copies, of the two-plane windows and of the red-black points), and at
-    // least the planes a window spans, K + 4 (two of them being loaded)
+    // least the planes a window spans, K + 4 with two of them being loaded
     static constexpr int PER = (K + 5) / 2 * 2;
+    // planes requested ahead of the one being computed (one where two and the
+    // reduction do not fit the registers of 16 waves)
+    static constexpr int LA = !PAIRS && RED ? 1 : 2;
     static constexpr int NH = RB ? PER : 2 * K;  // planes held
     // Without a fused reduction the right-hand side is held as h^2 f, formed
     // once per loaded value instead of once per level, and the operator is
     // given h^2 = 1: the product it forms is then exact, so every level
     // rounds as the plain sweep does.  (A fused residual needs f itself.)
     static constexpr bool PRE_H2 = HAS_F && !RED;
-    using Lds = T[2][K][R][RB ? 1 : 2][NL];
+    using Lds = T[2][K][R][NE][NL];
 
     const TBArgs& a;
     Lds& lds;
@@ -179,20 +191,20 @@ struct TBMarch {
     const T* fb;
     T* ob;
     int z0, z1, s_end;
-    int l, idx, dn, up;          // lane of the half-wave; LDS slots of this lane and the half-waves below / above
-    uint32_t roff[R];            // byte offset of this lane's pair in a plane
-    int d1;                      // byte distance to the pair's second point (sizeof(T) unless a wrap splits it)
+    int idx, dn, up;             // LDS slots of this lane and of the same columns in the rows below / above
+    uint32_t roff[R];            // byte offset of this lane's columns in a plane
+    int d1;                      // SPLIT: byte distance to the pair's second column
     bool whole;                  // rows are whole pairs
     bool dir;                    // Dirichlet rule
     // lane masks (scalar registers): inside the grid in x and y (periodic
     // rule: any); the pair's points are written
-    uint64_t keep[R][2], out0[R], out1[R];
+    uint64_t keep[R][NV], out[R][NV];
     T bcv, omega, h2;
     // RB: plane p in slot p mod PER (by the step's phase); else level L's two
     // newest planes in 2 L, 2 L + 1, and nu the two planes being loaded
-    T u[NH][R][2];
-    T nu[2][R][2];
-    T fq[PER][R][2];             // h^2 f (or f) of plane p in slot p mod PER
+    T u[NH][R][NV];
+    T nu[2][R][NV];
+    T fq[PER][R][NV];            // h^2 f (or f) of plane p in slot p mod PER
 
     // Plane offsets (elements): the input's next plane is zn, kept wrapped
     // under the periodic rule and clamped at use under Dirichlet's; the
@@ -206,14 +218,14 @@ struct TBMarch {
         if (!dir && zn == nz) zn = 0;
         return (int64_t)zz * a.g.pz;
     }
-    __device__ __forceinline__ void load_pair(const char* pl, int i, T (&v)[2]) const {
-        if (SPLIT) {
+    __device__ __forceinline__ void load_row(const char* pl, int i, T (&v)[NV]) const {
+        if constexpr (SPLIT) {
             v[0] = *reinterpret_cast<const T*>(pl + roff[i]);
-            v[1] = *reinterpret_cast<const T*>(pl + (uint32_t)((int)roff[i] + d1));
+            v[NV - 1] = *reinterpret_cast<const T*>(pl + (uint32_t)((int)roff[i] + d1));
         } else {
-            const Vec<T, 2> q = *reinterpret_cast<const Vec<T, 2>*>(pl + roff[i]);
-            v[0] = q.v[0];
-            v[1] = q.v[1];
+            const Vec<T, NV> q = *reinterpret_cast<const Vec<T, NV>*>(pl + roff[i]);
+#pragma unroll
+            for (int e = 0; e < NV; ++e) v[e] = q.v[e];
         }
     }
     // Request the next plane of the input (PH: the phase of its step) and the
@@ -223,11 +235,11 @@ struct TBMarch {
         const int64_t off = next_off();
         const char* pu = reinterpret_cast<const char*>(ub + off);
 #pragma unroll
-        for (int i = 0; i < R; ++i) load_pair(pu, i, RB ? u[RB ? PH % PER : 0][i] : nu[PH & 1][i]);
+        for (int i = 0; i < R; ++i) load_row(pu, i, RB ? u[RB ? PH % PER : 0][i] : nu[PH & 1][i]);
         if (HAS_F && F) {
             const char* pf = reinterpret_cast<const char*>(fb + foff);
 #pragma unroll
-            for (int i = 0; i < R; ++i) load_pair(pf, i, fq[(PH + PER - 1) % PER][i]);
+            for (int i = 0; i < R; ++i) load_row(pf, i, fq[(PH + PER - 1) % PER][i]);
         }
         foff = off;
     }
@@ -240,24 +252,24 @@ struct TBMarch {
         auto slot = [](int j) constexpr { return ((PH - j) % PER + PER) % PER; };
         constexpr int par = PH & 1;
         // plane s arrives: boundary values, and h^2 f of plane s - 1
-        T cur[R][2];  // Jacobi: level 0 of plane s
+        T cur[R][NV];  // Jacobi: level 0 of plane s
         {
             const bool z_in = !dir || ((unsigned)s < (unsigned)a.g.nz);
 #pragma unroll
             for (int i = 0; i < R; ++i)
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
+                for (int e = 0; e < NV; ++e) {
                     T& v = RB ? u[RB ? slot(0) : 0][i][e] : nu[par][i][e];
                     cur[i][e] = v = lane_of(z_in ? keep[i][e] : 0) ? v : bcv;
                     if (PRE_H2) fq[slot(1)][i][e] = exact_mul(h2, fq[slot(1)][i][e]);
                 }
         }
-        // request plane s + TB_LA of the input, the one before of the right-hand side
+        // request plane s + LA of the input, the one before of the right-hand side
         // (redefined each step: the 64-bit form of the offsets is then not kept
         // in registers, and accesses take a scalar base and a 32-bit offset)
 #pragma unroll
         for (int i = 0; i < R; ++i) asm volatile("" : "+v"(roff[i]));
-        load_next<PH + TB_LA, true>();
+        load_next<PH + LA, true>();
         const int lv = WARM ? (s - (z0 - K)) >> 1 : K;  // levels needed so far
         // stage level t-1 of plane s - t (RB: the points this step does not update)
         auto& lb = lds[par];
@@ -265,15 +277,11 @@ struct TBMarch {
         for (int t = 1; t <= K; ++t)
             if (!WARM || t <= lv) {
 #pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    if (RB) {
-                        lb[t - 1][i][0][idx] = u[RB ? slot(t) : 0][i][1 - ((i + PH) & 1)];
-                    } else {
-                        // (the points of a pair in two rows of the copy: no bank conflicts)
-                        lb[t - 1][i][0][idx] = u[RB ? 0 : 2 * (t - 1) + 1][i][0];
-                        lb[t - 1][i][RB ? 0 : 1][idx] = u[RB ? 0 : 2 * (t - 1) + 1][i][1];
-                    }
-                }
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int e = 0; e < NE; ++e)  // (a pair in two rows of the copy: no bank conflicts)
+                        lb[t - 1][i][e][idx] =
+                            RB ? u[RB ? slot(t) : 0][i][NV - 1 - ((i + PH) & 1)] : u[RB ? 0 : 2 * (t - 1) + 1][i][e];
             }
         __syncthreads();
         const T inv = T(1) / T(6), h2l = PRE_H2 ? T(1) : h2;
@@ -281,24 +289,24 @@ struct TBMarch {
         for (int t = 1; t <= K; ++t) {
             const int zp = s - t;
             const bool z_in = !dir || ((unsigned)zp < (unsigned)a.g.nz);
-            T c[R][2], val[R][2];
-            double rv[R][2];
+            T c[R][NV], val[R][NV];
+            double rv[R][NV];
             if (!RB) {
 #pragma unroll
                 for (int i = 0; i < R; ++i)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) val[i][e] = c[i][e] = u[RB ? 0 : 2 * (t - 1) + 1][i][e];
+                    for (int e = 0; e < NV; ++e) val[i][e] = c[i][e] = u[RB ? 0 : 2 * (t - 1) + 1][i][e];
             }
             if (!WARM || t <= lv) {
 #pragma unroll
                 for (int i = 0; i < R; ++i)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < NV; ++e) {
                         if (RB && e != ((i + PH) & 1)) continue;
                         T old, sum;
                         if (RB) {
                             auto& q = u[RB ? slot(t) : 0];
-                            const T xs = q[i][1 - e];
+                            const T xs = q[i][NV - 1 - e];
                             const T xm = e == 0 ? lane_shift<DPP_WAVE_SHR1>(xs) : xs;
                             const T xp = e == 0 ? xs : lane_shift<DPP_WAVE_SHL1>(xs);
                             const T ym = i > 0 ? q[0][e] : lb[t - 1][1][0][dn];
@@ -306,8 +314,8 @@ struct TBMarch {
                             sum = near_sum(xp, xm, yp, ym, u[RB ? slot(t - 1) : 0][i][e], u[RB ? slot(t + 1) : 0][i][e]);
                             old = q[i][e];
                         } else {
-                            const T xm = e == 0 ? lane_shift<DPP_WAVE_SHR1>(c[i][1]) : c[i][0];
-                            const T xp = e == 0 ? c[i][1] : lane_shift<DPP_WAVE_SHL1>(c[i][0]);
+                            const T xm = e == 0 ? lane_shift<DPP_WAVE_SHR1>(c[i][NV - 1]) : c[i][0];
+                            const T xp = e == NV - 1 ? lane_shift<DPP_WAVE_SHL1>(c[i][0]) : c[i][NV - 1];
                             const T ym = i > 0 ? c[0][e] : lb[t - 1][1][RB ? 0 : e][dn];
                             const T yp = i > 0 ? lb[t - 1][0][RB ? 0 : e][up] : c[1][e];
                             sum = near_sum(xp, xm, yp, ym, cur[i][e], u[RB ? 0 : 2 * (t - 1)][i][e]);
@@ -332,24 +340,25 @@ struct TBMarch {
                 char* po = reinterpret_cast<char*>(ob + (int64_t)zp * a.g.pz);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    Vec<T, 2> q;
+                    Vec<T, NV> q;
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < NV; ++e) {
                         q.v[e] = RB ? u[RB ? slot(t) : 0][i][e] : val[i][e];
                         // keep the computation out of the branches below
                         asm volatile("" : "+v"(q.v[e]));
                     }
-                    if (whole) {
-                        if (lane_of(out0[i])) *reinterpret_cast<Vec<T, 2>*>(po + roff[i]) = q;
+                    if (!PAIRS || whole) {
+                        if (lane_of(out[i][0])) *reinterpret_cast<Vec<T, NV>*>(po + roff[i]) = q;
                     } else {
-                        if (lane_of(out0[i])) *reinterpret_cast<T*>(po + roff[i]) = q.v[0];
-                        if (lane_of(out1[i])) *reinterpret_cast<T*>(po + roff[i] + sizeof(T)) = q.v[1];
+#pragma unroll
+                        for (int e = 0; e < NV; ++e)
+                            if (lane_of(out[i][e])) *reinterpret_cast<T*>(po + roff[i] + e * sizeof(T)) = q.v[e];
                     }
                     if (RED) {
 #pragma unroll
-                        for (int e = 0; e < 2; ++e) {
+                        for (int e = 0; e < NV; ++e) {
                             if (RB && e != ((i + PH) & 1)) continue;
-                            if (lane_of(e == 0 ? out0[i] : out1[i])) acc = red_acc(acc, rv[i][e], a.ra.op);
+                            if (lane_of(out[i][e])) acc = red_acc(acc, rv[i][e], a.ra.op);
                         }
                     }
                 }
@@ -360,7 +369,7 @@ struct TBMarch {
 #pragma unroll
                 for (int i = 0; i < R; ++i)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < NV; ++e) {
                         u[RB ? 0 : 2 * (t - 1)][i][e] = c[i][e];
                         u[RB ? 0 : 2 * (t - 1) + 1][i][e] = cur[i][e];
                         cur[i][e] = val[i][e];
@@ -389,7 +398,7 @@ __device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double
     // step: a step's staging writes the copy the previous step did not read,
     // so one barrier per step suffices
     __shared__ typename M::Lds lds;
-    constexpr int R = TB_RPL, G = tb_ghost_x(K);
+    constexpr int R = M::R, NV = M::NV, G = tb_ghost_x(K, M::PAIRS), GROUP = M::GROUP;
     const Geo& g = a.g;
     M m{a, lds, acc};
     m.ub = static_cast<const T*>(a.u);
@@ -402,40 +411,46 @@ __device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double
     m.bcv = (T)g.bcv;
     m.omega = (T)a.p[0];
     m.h2 = (T)a.p[1];
-    const int rg = threadIdx.x >> 5;  // half-wave: rows 2 rg, 2 rg + 1 of the region
-    m.l = threadIdx.x & 31;
+    const int rg = M::PAIRS ? threadIdx.x / GROUP : __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP);
+    const int l = threadIdx.x % GROUP;
     m.idx = threadIdx.x;
     // (the region's edge rows read their own: they lie in the ghost zone)
-    m.dn = rg > 0 ? m.idx - 32 : m.idx;
-    m.up = rg < 2 * TB_NW - 1 ? m.idx + 32 : m.idx;
-    const int x = xt * tb_out_x(K) - G + 2 * m.l;  // even
+    m.dn = rg > 0 ? m.idx - GROUP : m.idx;
+    m.up = rg < TB_ROWS / R - 1 ? m.idx + GROUP : m.idx;
+    const int x = xt * tb_out_x(K, M::PAIRS) - G + NV * l;  // pairs: even
     const int rule = m.dir ? BC_CLAMP : g.bc;
     m.whole = (g.nx & 1) == 0;
-    // x even: a pair inside the grid, or starting at its last column (the
-    // second point is then the row's padding, never used), is contiguous; a
-    // pair outside under the Dirichlet rule is read anywhere and replaced
-    const int xs = (unsigned)x < (unsigned)g.nx ? x : (m.dir ? (x < 0 ? 0 : (g.nx - 1) & ~1) : wrap_idx(x, g.nx, rule));
-    m.d1 = !SPLIT ? (int)sizeof(T) : (wrap_idx(x + 1, g.nx, rule) - xs) * (int)sizeof(T);
+    // a pair inside the grid, or starting at its last column (the second point
+    // is then the row's padding, never used), is contiguous; columns outside
+    // under the Dirichlet rule are read anywhere in the row and replaced
+    const int xs = (unsigned)x < (unsigned)g.nx ? x : (m.dir ? (x < 0 ? 0 : (g.nx - 1) & -NV) : wrap_idx(x, g.nx, rule));
+    m.d1 = SPLIT ? (wrap_idx(x + 1, g.nx, rule) - xs) * (int)sizeof(T) : 0;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         const int row = rg * R + i, y = yt * tb_out_y(K) - K + row;
         const bool y_in = (unsigned)y < (unsigned)g.ny;
         const int ys = y_in ? y : wrap_idx(y, g.ny, rule);
         m.roff[i] = (uint32_t)(((int64_t)ys * g.py + xs) * (int64_t)sizeof(T));
+        const bool out = row >= K && row < TB_ROWS - K && y_in && l >= G / NV && l < (TB_COLS - G) / NV;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) m.keep[i][e] = __ballot(!m.dir || (y_in && (unsigned)(x + e) < (unsigned)g.nx));
-        const bool out = row >= K && row < TB_ROWS - K && y_in && m.l >= G / 2 && m.l < (TB_COLS - G) / 2 && x < g.nx;
-        m.out0[i] = __ballot(out);
-        m.out1[i] = __ballot(out && x + 1 < g.nx);
+        for (int e = 0; e < NV; ++e) {
+            const bool x_in = (unsigned)(x + e) < (unsigned)g.nx;
+            m.keep[i][e] = __ballot(!m.dir || (y_in && x_in));
+            m.out[i][e] = __ballot(out && x_in);
+        }
     }
 #pragma unroll
     for (int j = 0; j < M::NH; ++j)
 #pragma unroll
-        for (int i = 0; i < R; ++i) m.u[j][i][0] = m.u[j][i][1] = T(0);
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int e = 0; e < NV; ++e) m.u[j][i][e] = T(0);
 #pragma unroll
     for (int j = 0; j < M::PER; ++j)
 #pragma unroll
-        for (int i = 0; i < R; ++i) m.fq[j][i][0] = m.fq[j][i][1] = T(0);
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int e = 0; e < NV; ++e) m.fq[j][i][e] = T(0);
 
     // Level K is first needed at plane z0 in step z0 + K; steps from z0 - K on
     // fill the windows.  RB: the point (x + e, y, s - t) of row i has colour
@@ -447,8 +462,7 @@ __device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double
     m.s_end = m.z1 + K;
     m.zn = m.dir ? s : wrap_idx(s, g.nz, BC_PERIODIC);
     m.template load_next<0, false>();
-    m.template load_next<1, true>();
-    static_assert(TB_LA == 2, "planes requested before the march");
+    if constexpr (M::LA == 2) m.template load_next<1, true>();
     // (a group is at least 2 K steps)
     if (m.template group<0, true>(s)) return;
     while (!m.template group<0, false>(s)) {
@@ -456,7 +470,7 @@ __device__ __forceinline__ void tb7_tile(const TBArgs& a, const int tile, double
 }
 
 template <class T, bool HAS_F, int K, bool RED, bool RB, bool SPLIT>
-__global__ __launch_bounds__(64 * TB_NW, (tb_waves_per_eu<T, K, RB>())) void tb7_sweep(TBArgs a) {
+__global__ __launch_bounds__(64 * tb_waves(tb_pairs(sizeof(T) == 8, RB)), (tb_waves_per_eu<T, K, RB>())) void tb7_sweep(TBArgs a) {
     const int tile = xcd_remap(blockIdx.x, a.ntx * a.nty * a.ncz);
     double acc = 0.0;
     tb7_tile<T, HAS_F, K, RED, RB, SPLIT>(a, tile, acc);
