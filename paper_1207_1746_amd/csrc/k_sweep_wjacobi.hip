@@ -42,4 +42,8 @@ hipError_t launch_poisson_resid(TArgs& a, const TileCfg& c, bool red, hipStream_
     return run7<OpPoissonResid>(a, c, red, s, nb);
 }
 
+hipError_t launch_poisson_norm(TArgs& a, const TileCfg& c, hipStream_t s, int* nb) {
+    return run7<OpPoissonNorm>(a, c, true, s, nb);
+}
+
 }  // namespace gk

@@ -120,6 +120,11 @@ struct OpPoissonResid {
     }
 };
 
+// Its norm alone (a fused reduction, nothing stored).
+struct OpPoissonNorm : OpPoissonResid {
+    static constexpr bool STORES = false;
+};
+
 // Variable-coefficient 7-point operator over 9 input grids writing 3 outputs.
 //   pointwise A = c0..c6, s.  out = {u', r, |F|}.
 template <class T_, class S_>

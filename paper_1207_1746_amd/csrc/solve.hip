@@ -27,15 +27,18 @@ struct TmpGrid {
 
 size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 
-// Poisson chunks on grids of at least 72^3 points run temporally blocked
-// passes (whole solves measured 1.3-1.8 x faster at 80^3-112^3; 4-10%
-// slower at 64^3, and at 128^3, where the plain tiles fit the grid exactly),
-// unless a plane spans 4 GiB or more (the blocked kernels' in-plane offsets
-// are 32-bit; the plain sweeps serve such grids).
+// Poisson chunks run temporally blocked passes (a pass of four sweeps takes
+// 10 us at 32^3 and 13 at 64^3, a plain sweep 5 at either), unless a plane
+// spans 4 GiB or more (the blocked kernels' in-plane offsets are 32-bit; the
+// plain sweeps serve such grids).
 bool blocked_passes(const gscl_grid_desc& d) {
-    const bool plane_fits = ((d.n[1] - 1) * d.pitch[0] + d.n[0]) * (int64_t)sizeof(double) <= (int64_t)UINT32_MAX;
-    return plane_fits && d.n[0] * d.n[1] * d.n[2] >= (int64_t)72 * 72 * 72;
+    return ((d.n[1] - 1) * d.pitch[0] + d.n[0]) * (int64_t)sizeof(double) <= (int64_t)UINT32_MAX;
 }
+
+// Workspace that a red-black solve cannot do without, below which it is
+// refused; without room for the ping-pong grid of blocked passes on top, its
+// colour passes run in place.
+size_t rbgs_least_bytes(const gscl_grid_desc& d);
 
 // Split n sweeps (or colour passes) into passes of at most TB_KMAX, with an
 // even pass count so that a ping-pong chunk ends in the caller's grid.
@@ -98,12 +101,17 @@ struct Cleanup {
     }
 };
 
+size_t rbgs_least_bytes(const gscl_grid_desc& d) {
+    const bool large = d.n[0] * d.n[1] * d.n[2] >= (int64_t)72 * 72 * 72;
+    return bytes_like(d, GSCL_F32) + (large && blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
+}
+
 }  // namespace
 
 extern "C" size_t gscl_solve_workspace_bytes(const gscl_solve_desc* sd, const gscl_grid* x, int nf) {
     if (!sd || !grid_ok(x) || nf < 1) return 0;
     const gscl_grid_desc& d = x->d;
-    if (sd->kind == GSCL_K_RBGS)  // residual grid, and the ping-pong grid of blocked passes
+    if (sd->kind == GSCL_K_RBGS)  // the ping-pong grid of blocked passes, and what the least counts
         return bytes_like(d, GSCL_F32) + (blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
     if (sd->precision == GSCL_PREC_F64) return bytes_like(d, GSCL_F64) * nf + 256;
     const int s = inner_dtype(sd->precision);
@@ -114,6 +122,34 @@ extern "C" size_t gscl_solve_workspace_bytes(const gscl_solve_desc* sd, const gs
 static int sync_read(gscl_ctx* c, double* host) {
     GSCL_HIP(hipMemcpyAsync(host, c->result + 8, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     GSCL_HIP(hipStreamSynchronize(c->stream));
+    return GSCL_OK;
+}
+
+// ||b - A x||^2 into *result; x and b as the sweeps before it have checked
+// them.  Read-only, so short chunks cost little: 2048 blocks and up keep the
+// loads of every CU in flight (192^3: 53 us as a residual sweep of 288 blocks
+// that also writes the residual).
+static int poisson_norm(gscl_ctx* c, const gscl_grid* x, const gscl_grid* b, double h2, double* result) {
+    gk::TArgs a;
+    memset(&a, 0, sizeof a);
+    a.g = geo_of(x);
+    a.nb[0] = x->ptr;
+    a.pa[0] = b->ptr;
+    a.p[1] = h2;
+    a.p[2] = 1.0 / h2;
+    gk::TileCfg t;
+    t.V = a.g.nx >= 128 ? 2 : 1;
+    t.NW = 4;
+    const int64_t cols = ((int64_t)a.g.nx + 64 * t.V - 1) / (64 * t.V) * ((a.g.ny + 3) / 4);
+    t.cz = (int)std::min<int64_t>(std::max<int64_t>(cols * a.g.nz / 2048, 2), 32);
+    int nb = gk::tiled_blocks(a.g, t);
+    int rc = ensure_partials(c, nb);
+    if (rc) return rc;
+    a.ra.partials = c->partials;
+    a.ra.result = result;
+    a.ra.op = gk::R_SUMSQ;
+    a.ra.eps = 0.0;
+    GSCL_HIP(gk::launch_poisson_norm(a, t, c->stream, &nb));
     return GSCL_OK;
 }
 
@@ -154,7 +190,7 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
     // every row and plane start 16-byte aligned for the narrowest type too
     if (x[0]->d.pitch[0] % 16 || x[0]->d.pitch[1] % 16)
         return gscl_fail(GSCL_ERR_SHAPE, "solve needs row and plane pitches that are multiples of 16 elements");
-    const size_t need = gscl_solve_workspace_bytes(sd, x[0], nf);
+    const size_t need = rbgs ? rbgs_least_bytes(x[0]->d) : gscl_solve_workspace_bytes(sd, x[0], nf);
     if (!workspace || ws_bytes < need)
         return gscl_fail(GSCL_ERR_NOMEM, "workspace of %zu bytes needed", need);
     if (((uintptr_t)workspace) % 256) return gscl_fail(GSCL_ERR_ARG, "workspace must be 256-byte aligned");
@@ -207,11 +243,11 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
 
     if (rbgs) {
         // Red-black relaxation: a chunk is S sweeps (a red and a black pass
-        // each) and then the residual of the current x, so the grid returned
-        // is the grid that was checked.  On large grids the 2S colour passes
-        // run as blocked passes of up to TB_KMAX colour passes, ping-ponging
-        // through a workspace grid (an even count, so the chunk ends in x);
-        // elsewhere each colour pass runs in place.  omega = 0 selects the
+        // each) and then the residual norm of the current x, so the grid
+        // returned is the grid that was checked.  The 2S colour passes run as
+        // blocked passes of up to TB_KMAX colour passes, ping-ponging through a
+        // workspace grid (an even count, so the chunk ends in x); where that
+        // cannot be, each colour pass runs in place.  omega = 0 selects the
         // optimal SOR weight of the model problem, 2 / (1 + sqrt(1 - rho^2)),
         // rho = (cos(pi/(nx+1)) + cos(pi/(ny+1)) + cos(pi/(nz+1))) / 3 the
         // Jacobi spectral radius for a uniform grid spacing.
@@ -221,9 +257,8 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
             const double rho = (cos(pi / (xd.n[0] + 1)) + cos(pi / (xd.n[1] + 1)) + cos(pi / (xd.n[2] + 1))) / 3.0;
             omega = 2.0 / (1.0 + sqrt(1.0 - rho * rho));
         }
-        gscl_grid* r = carve(c, xd, GSCL_F32, 0, cur, cl.grids);
         const int S = sd->check_every;
-        const bool tb = blocked_passes(xd);
+        const bool tb = blocked_passes(xd) && ws_bytes >= bytes_like(xd, GSCL_F64) + 256;
         gscl_grid* w = tb ? carve(c, xd, GSCL_F64, 1, cur, cl.grids) : nullptr;
         const std::vector<int> passes = tb ? split_passes(2 * S) : std::vector<int>(2 * S, 1);
         if ((rc = gscl_graph_begin(c))) return rc;
@@ -248,14 +283,7 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
             rc = gscl_do_all(c, &op, in, 2, &dst, 1, nullptr, nullptr);
             colour = (colour + passes[q]) & 1;
         }
-        if (rc == GSCL_OK) {
-            gscl_stencil_desc op;
-            memset(&op, 0, sizeof op);
-            op.kind = GSCL_K_POISSON_RESID;
-            op.p[1] = sd->h2;
-            gscl_grid* in[2] = {x[0], const_cast<gscl_grid*>(b[0])};
-            rc = gscl_do_all(c, &op, in, 2, &r, 1, &chk, nullptr);
-        }
+        if (rc == GSCL_OK) rc = poisson_norm(c, x[0], b[0], sd->h2, (double*)chk.dev_result);
         gscl_graph* gr = nullptr;
         int rc2 = gscl_graph_end(c, &gr);
         if (rc) return rc;

@@ -46,6 +46,10 @@ struct Star {
     int ix, iy, iz;  // index of the point (stateful operators query it)
 };
 
+// Operators store their outputs unless they say otherwise.
+template <class Op, class = void> struct Stores { static constexpr bool v = true; };
+template <class Op> struct Stores<Op, std::void_t<decltype(Op::STORES)>> { static constexpr bool v = Op::STORES; };
+
 template <int N> struct AtLeast1 { static constexpr int v = N > 0 ? N : 1; };
 
 // Load V elements of row (y, z) starting at gx, boundary-synthesized where
@@ -257,7 +261,7 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
             const int64_t off = rowoff + gx;
             if (gx + V <= g.nx) {
 #pragma unroll
-                for (int i = 0; i < NO; ++i) {
+                for (int i = 0; i < (Stores<Op>::v ? NO : 0); ++i) {
                     Vec<SO, V> vv;
 #pragma unroll
                     for (int v = 0; v < V; ++v) vv.v[v] = Store<SO>::cv(res[i][v]);
@@ -274,7 +278,7 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
                 for (int v = 0; v < V; ++v) {
                     if (gx + v < g.nx) {
 #pragma unroll
-                        for (int i = 0; i < NO; ++i)
+                        for (int i = 0; i < (Stores<Op>::v ? NO : 0); ++i)
                             static_cast<SO*>(a.out[i])[off + v] = Store<SO>::cv(res[i][v]);
                         if (RED) {
 #pragma unroll
