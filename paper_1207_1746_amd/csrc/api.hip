@@ -138,6 +138,7 @@ extern "C" int gscl_init(int device, gscl_ctx** out) {
     c->partials = nullptr;
     c->partial_cap = 0;
     c->result = nullptr;
+    c->host_result = nullptr;
     c->capturing = false;
     *out = c;
     return GSCL_OK;
@@ -194,6 +195,8 @@ extern "C" int gscl_begin(gscl_ctx* c, void* stream) {
     if (src) return src;
     c->stream = (hipStream_t)stream;
     if (!c->result) {
+        if (!c->host_result)
+            GSCL_HIP(hipHostMalloc((void**)&c->host_result, 64 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
         GSCL_HIP(hipMalloc(&c->result, 64 * sizeof(double)));
         GSCL_HIP(hipMemset(c->result, 0, 64 * sizeof(double)));
         int rc = ensure_partials(c, 1 << 16);
@@ -228,6 +231,7 @@ extern "C" int gscl_finalize(gscl_ctx* c) {
         hipFree(c->partials);
         hipFree(c->result);
     }
+    if (c->host_result) hipHostFree(c->host_result);
     c->magic = 0;
     c->state = CTX_FINALIZED;
     delete c;
@@ -463,7 +467,9 @@ static int tb_partials(gscl_ctx* c, const FixedScratch* fx, int kind, int dtype,
 
 static void fill_red(gscl_ctx* c, const gscl_reduce_desc* rd, gk::RedArgs& ra, const FixedScratch* fx = nullptr) {
     ra.partials = fx ? fx->partials : c->partials;
-    ra.result = rd && rd->dev_result ? (double*)rd->dev_result : (fx ? fx->result : c->result);
+    // a result for the host is stored to pinned memory by the kernel that forms
+    // it: one synchronization and no copy
+    ra.result = rd && rd->dev_result ? (double*)rd->dev_result : c->host_result;
     ra.op = rd ? rd->op : 0;
     ra.eps = rd ? rd->eps : 0.0;
 }
@@ -477,13 +483,11 @@ static int check_reduce_desc(const gscl_reduce_desc* rd, double* host_result, bo
     return GSCL_OK;
 }
 
-static int finish_reduce(gscl_ctx* c, const gscl_reduce_desc* rd, double* host_result,
-                         const FixedScratch* fx = nullptr) {
+static int finish_reduce(gscl_ctx* c, const gscl_reduce_desc* rd, double* host_result) {
     if (rd->dev_result) return GSCL_OK;
     if (c->capturing) return gscl_fail(GSCL_ERR_STATE, "host-result reduction inside graph capture");
-    GSCL_HIP(hipMemcpyAsync(host_result, fx ? fx->result : c->result, sizeof(double), hipMemcpyDeviceToHost,
-                            c->stream));
     GSCL_HIP(hipStreamSynchronize(c->stream));
+    *host_result = *(volatile double*)c->host_result;
     return GSCL_OK;
 }
 
@@ -843,7 +847,7 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
     }
     if (he == hipErrorInvalidValue) return gscl_fail(GSCL_ERR_UNSUPPORTED, "no kernel for this kind/dtype/tile");
     if (he != hipSuccess) return gscl_hip_fail(he, "kernel launch");
-    if (red) return finish_reduce(c, fused, fused_result, fx);
+    if (red) return finish_reduce(c, fused, fused_result);
     return GSCL_OK;
 }
 

@@ -87,12 +87,20 @@ int inner_dtype(int precision) {
 
 struct Cleanup {
     std::vector<gscl_grid*> grids;
-    gscl_graph* graph = nullptr;
+    gscl_graph* graph[2] = {nullptr, nullptr};
+    hipEvent_t event = nullptr;
+    bool in_place = false;  // red-black passes on x itself
     hipStream_t restore_stream = nullptr;
     gscl_ctx* ctx = nullptr;
     bool swapped = false;
     ~Cleanup() {
-        if (graph) gscl_graph_destroy(graph);
+        // (an early return may leave a pass running on the caller's workspace)
+        if (event) {
+            hipStreamSynchronize(ctx->stream);
+            hipEventDestroy(event);
+        }
+        for (gscl_graph* g : graph)
+            if (g) gscl_graph_destroy(g);
         for (auto* g : grids) {
             g->magic = 0;
             delete g;
@@ -119,10 +127,50 @@ extern "C" size_t gscl_solve_workspace_bytes(const gscl_solve_desc* sd, const gs
     return (bytes_like(d, GSCL_F32) + 3 * bytes_like(d, s)) * nf + 256;
 }
 
+// The norm a check kernel has stored to the context's pinned slot.
+static double* check_slot(gscl_ctx* c) { return c->host_result + 8; }
+
 static int sync_read(gscl_ctx* c, double* host) {
-    GSCL_HIP(hipMemcpyAsync(host, c->result + 8, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     GSCL_HIP(hipStreamSynchronize(c->stream));
+    *host = *(volatile double*)check_slot(c);
     return GSCL_OK;
+}
+
+// Chunks of S sweeps, each npasses passes (an even number, ping-ponging from x
+// and back) and a check of the x they leave, until done(norm^2) is nonzero or
+// the sweeps reach their limit.  Two graphs: the first pass, which only writes
+// the workspace, and the rest with the check; the first pass of the next chunk
+// is enqueued behind a check before the host waits for the check's norm, so the
+// GPU works through the wait and the next launch.  The last one is left over:
+// x is not touched by it.  (64^3 Jacobi, check every 32: 46.3 -> 41 ms.)
+template <class Pass, class Check, class Done>
+static int run_chunks(gscl_ctx* c, Cleanup& cl, size_t npasses, int S, int64_t max_sweeps, int64_t& sweeps, Pass&& pass,
+                      Check&& check, Done&& done) {
+    auto capture = [&](gscl_graph*& g, size_t from, size_t to, bool with_check) -> int {
+        int rc = gscl_graph_begin(c);
+        if (rc) return rc;
+        for (size_t q = from; q < to && rc == GSCL_OK; ++q) rc = pass(q);
+        if (rc == GSCL_OK && with_check) rc = check();
+        const int rc2 = gscl_graph_end(c, &g);
+        return rc ? rc : rc2;
+    };
+    const size_t head = cl.in_place ? 0 : 1;  // in-place passes write x: nothing runs ahead
+    int rc;
+    if (head && (rc = capture(cl.graph[0], 0, head, false))) return rc;
+    if ((rc = capture(cl.graph[1], head, npasses, true))) return rc;
+    GSCL_HIP(hipEventCreateWithFlags(&cl.event, hipEventDisableTiming));
+    if (head && (rc = gscl_graph_launch(c, cl.graph[0]))) return rc;
+    while (sweeps < max_sweeps) {
+        if ((rc = gscl_graph_launch(c, cl.graph[1]))) return rc;
+        GSCL_HIP(hipEventRecord(cl.event, c->stream));
+        sweeps += S;
+        if (head && sweeps < max_sweeps && (rc = gscl_graph_launch(c, cl.graph[0]))) return rc;
+        GSCL_HIP(hipEventSynchronize(cl.event));
+        const int d = done(*(volatile double*)check_slot(c));
+        if (d < 0) return d;
+        if (d == 1) return GSCL_OK;
+    }
+    return GSCL_ERR_NOCONV;
 }
 
 // ||b - A x||^2 into *result; x and b as the sweeps before it have checked
@@ -234,7 +282,7 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
     }
     // worst-case reduction partials for any launch below, before any capture
     if ((rc = gscl_reserve(c, xd.n[0] * xd.n[1] * xd.n[2] * 2 + 4096))) return rc;
-    gscl_reduce_desc chk{GSCL_R_SUMSQ, GSCL_RV_RESIDUAL, 0.0, c->result + 8};
+    gscl_reduce_desc chk{GSCL_R_SUMSQ, GSCL_RV_RESIDUAL, 0.0, check_slot(c)};
     auto done_check = [&](double res2) -> int {
         if (res2 != res2) return gscl_fail(GSCL_ERR_NUMERIC, "residual is NaN after %lld sweeps", (long long)sweeps);
         rel = sqrt(res2 / bnorm2);
@@ -261,9 +309,9 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
         const bool tb = blocked_passes(xd) && ws_bytes >= bytes_like(xd, GSCL_F64) + 256;
         gscl_grid* w = tb ? carve(c, xd, GSCL_F64, 1, cur, cl.grids) : nullptr;
         const std::vector<int> passes = tb ? split_passes(2 * S) : std::vector<int>(2 * S, 1);
-        if ((rc = gscl_graph_begin(c))) return rc;
+        cl.in_place = !tb;
         int colour = 0;
-        for (size_t q = 0; q < passes.size() && rc == GSCL_OK; ++q) {
+        auto pass = [&](size_t q) -> int {
             gscl_stencil_desc op;
             memset(&op, 0, sizeof op);
             op.p[0] = omega;
@@ -280,29 +328,12 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
                 op.kind = GSCL_K_RBGS;
             }
             gscl_grid* in[2] = {src, const_cast<gscl_grid*>(b[0])};
-            rc = gscl_do_all(c, &op, in, 2, &dst, 1, nullptr, nullptr);
             colour = (colour + passes[q]) & 1;
-        }
-        if (rc == GSCL_OK) rc = poisson_norm(c, x[0], b[0], sd->h2, (double*)chk.dev_result);
-        gscl_graph* gr = nullptr;
-        int rc2 = gscl_graph_end(c, &gr);
-        if (rc) return rc;
-        if (rc2) return rc2;
-        cl.graph = gr;
-        rc = GSCL_ERR_NOCONV;
-        while (sweeps < sd->max_sweeps) {
-            int e = gscl_graph_launch(c, gr);
-            if (e) return e;
-            sweeps += S;
-            double res2 = 0.0;
-            if ((e = sync_read(c, &res2))) return e;
-            int d = done_check(res2);
-            if (d < 0) return d;
-            if (d == 1) {
-                rc = GSCL_OK;
-                break;
-            }
-        }
+            return gscl_do_all(c, &op, in, 2, &dst, 1, nullptr, nullptr);
+        };
+        auto check = [&]() -> int { return poisson_norm(c, x[0], b[0], sd->h2, check_slot(c)); };
+        rc = run_chunks(c, cl, passes.size(), S, sd->max_sweeps, sweeps, pass, check, done_check);
+        if (rc != GSCL_OK && rc != GSCL_ERR_NOCONV) return rc;
     } else if (sd->precision == GSCL_PREC_F64) {
         std::vector<gscl_grid*> w(nf);
         for (int f = 0; f < nf; ++f) w[f] = carve(c, xd, GSCL_F64, R, cur, cl.grids);
@@ -313,9 +344,8 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
         // pass is one sweep.  The pass count is kept even so the chunk ends in x.
         const bool tb = poisson && blocked_passes(xd);
         const std::vector<int> passes = tb ? split_passes(S) : std::vector<int>(S, 1);
-        // capture one chunk: x -> w -> x ...
-        if ((rc = gscl_graph_begin(c))) return rc;
-        for (size_t q = 0; q < passes.size() && rc == GSCL_OK; ++q) {
+        // x -> w -> x ...; the last pass also reduces the residual of its input
+        auto pass = [&](size_t q) -> int {
             const bool odd = q % 2 == 0;
             std::vector<gscl_grid*> in, out;
             for (int f = 0; f < nf; ++f) {
@@ -331,36 +361,18 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
                 op.p[1] = sd->h2;
                 op.p[2] = passes[q];
                 in.push_back(const_cast<gscl_grid*>(b[0]));
-                rc = gscl_do_all(c, &op, in.data(), 2, out.data(), 1, red, nullptr);
-            } else {
-                op.kind = GSCL_K_VC13_JACOBI;
-                op.p[0] = sd->kappa;
-                op.p[1] = sd->omega;
-                op.p[2] = nf;
-                for (int f = 0; f < nf; ++f) in.push_back(const_cast<gscl_grid*>(b[f]));
-                for (int k2 = 0; k2 < 10; ++k2) in.push_back(const_cast<gscl_grid*>(coef[k2]));
-                rc = gscl_do_all(c, &op, in.data(), (int)in.size(), out.data(), nf, red, nullptr);
+                return gscl_do_all(c, &op, in.data(), 2, out.data(), 1, red, nullptr);
             }
-        }
-        gscl_graph* gr = nullptr;
-        int rc2 = gscl_graph_end(c, &gr);
-        if (rc) return rc;
-        if (rc2) return rc2;
-        cl.graph = gr;
-        rc = GSCL_ERR_NOCONV;
-        while (sweeps < sd->max_sweeps) {
-            int e = gscl_graph_launch(c, gr);
-            if (e) return e;
-            sweeps += S;
-            double res2 = 0.0;
-            if ((e = sync_read(c, &res2))) return e;
-            int d = done_check(res2);
-            if (d < 0) return d;
-            if (d == 1) {
-                rc = GSCL_OK;
-                break;
-            }
-        }
+            op.kind = GSCL_K_VC13_JACOBI;
+            op.p[0] = sd->kappa;
+            op.p[1] = sd->omega;
+            op.p[2] = nf;
+            for (int f = 0; f < nf; ++f) in.push_back(const_cast<gscl_grid*>(b[f]));
+            for (int k2 = 0; k2 < 10; ++k2) in.push_back(const_cast<gscl_grid*>(coef[k2]));
+            return gscl_do_all(c, &op, in.data(), (int)in.size(), out.data(), nf, red, nullptr);
+        };
+        rc = run_chunks(c, cl, passes.size(), S, sd->max_sweeps, sweeps, pass, [] { return GSCL_OK; }, done_check);
+        if (rc != GSCL_OK && rc != GSCL_ERR_NOCONV) return rc;
     } else {
         const int s = inner_dtype(sd->precision);
         const int m = sd->inner_sweeps;
