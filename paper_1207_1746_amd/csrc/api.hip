@@ -264,7 +264,7 @@ gk::TileCfg pick_tile(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d)
         // several waves, fewer on small images, where a wave's march is one
         // row's latency per step (4 x 8192^2: 8 rows 232 us, 4 rows 226, 2
         // rows 273; 1920 x 1080: 8 rows 11.8 us, 4 rows 7.7, 2 rows 6.6)
-        const int64_t rows = (nx + 1023) / 1024 * d.n[1] * d.n[2];
+        const int64_t rows = (nx + 1023) / 1024 * d.n[1] * d.n[2] * gk::image_lanes(nx) / 64;
         t.V = 4;
         t.NW = 4;
         t.cz = rows >= 8192 ? 4 : (rows >= 4096 ? 2 : 1);

@@ -22,7 +22,9 @@
 // pixel (one bit-select per dword, precomputed masks) and its last lane stores
 // its 1..15 pixels as 8, 4, 2 and 1.  Bound by HBM (1 B read, 3 B written per
 // pixel): 4 x 8192^2 225 us on fresh buffers, 4.8 TB/s (a device copy of that
-// size reaches 5.2).  8 x 1918 x 1078, 8-neighbour Laplacian: 76.7 -> 20.5 us
+// size reaches 5.2).  Rows of up to 512 pixels share a wave: 2, 4 or 8 chunks of
+// rows, each on as many lanes as its row needs (4 x 137 x 4145: 18.9 us with a
+// row per wave, 16.7 with a thread per pixel, 9.7 so).  8 x 1918 x 1078, 8-neighbour Laplacian: 76.7 -> 20.5 us
 // (before, widths that are not a multiple of 16 and the 8-neighbour Laplacian
 // ran one thread per pixel with 25 byte loads).
 #include "launch.h"
@@ -76,19 +78,20 @@ __device__ __forceinline__ uint32_t pk_sub16(uint32_t a, uint32_t b) {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-// The 16 int16 values of a lane are segments 2 lane, 2 lane + 1 (16 bytes
-// each) of the wave's 2 KB: hand them round so that lane t holds segments t
-// and 64 + t and each store instruction writes 1 KB contiguously (stored as
+// The 16 int16 values of lane t of P are segments 2 t, 2 t + 1 (16 bytes each) of
+// the P lanes' 32 P bytes: hand them round so that lane t holds segments t
+// and P + t and each store instruction writes 16 P bytes contiguously (stored as
 // they lie, every other 16 bytes per instruction, streaming stores leave
 // half-written lines: writes 1.12 x algorithmic and 254 us against 165 on
 // 4 x 8192^2).
+template <int P>
 __device__ __forceinline__ void exchange(const uint32_t (&lo)[8], u32x4& s0, u32x4& s1) {
-    const int lane = threadIdx.x & 63, src = lane >> 1;
+    const int lane = threadIdx.x & 63, src = (lane & ~(P - 1)) + (lane % P >> 1);
     const bool hi = lane & 1;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const uint32_t a0 = (uint32_t)__shfl((int)lo[k], src), b0 = (uint32_t)__shfl((int)lo[4 + k], src);
-        const uint32_t a1 = (uint32_t)__shfl((int)lo[k], src + 32), b1 = (uint32_t)__shfl((int)lo[4 + k], src + 32);
+        const uint32_t a1 = (uint32_t)__shfl((int)lo[k], src + P / 2), b1 = (uint32_t)__shfl((int)lo[4 + k], src + P / 2);
         s0[k] = hi ? b0 : a0;
         s1[k] = hi ? b1 : a1;
     }
@@ -105,12 +108,13 @@ __device__ __forceinline__ void store_seg(int16_t* p, const u32x4& v, int n) {
     if (n & 1) p[n & 6] = (int16_t)((n & 4) ? ((n & 2) ? v[3] : v[2]) : ((n & 2) ? v[1] : v[0]));
 }
 
-// One wave's march (64 lanes x 16 pixels, rows ys, ys + dir, ...).
-template <bool LAP8, bool TAIL>
+// A march of P lanes x 16 pixels over the n rows ys, ys + dir, ... (the wave's
+// other lanes march over rows of their own, all of them `steps` steps).
+template <bool LAP8, bool TAIL, int P>
 __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uint8_t* __restrict__ box,
                                             int16_t* __restrict__ lap, const Geo& g, int xw, int z, int ys, int dir,
-                                            int n) {
-    const int lane = threadIdx.x & 63;
+                                            int n, int steps) {
+    const int lane = threadIdx.x % P;
     const int xl = xw + lane * 16;
     const int nv = min(g.nx - xl, 16);         // this lane's pixels (<= 0: none)
     const int x = TAIL && nv <= 0 ? xw : xl;   // lanes past the end repeat the first lane's loads
@@ -133,11 +137,11 @@ __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uin
 
     // two rows in flight ahead of the one being consumed
     Row6 nxt1, nxt2;
-    if (1 < n) nxt1 = load_row6<TAIL>(img, g, x, ys + dir * 3, z, m);
-    for (int s = 0; s < n; ++s) {
+    if (1 < steps) nxt1 = load_row6<TAIL>(img, g, x, ys + dir * 3, z, m);
+    for (int s = 0; s < steps; ++s) {
         const int y = ys + dir * s;
-        const bool more = s + 1 < n;
-        if (s + 2 < n) nxt2 = load_row6<TAIL>(img, g, x, ys + dir * (s + 4), z, m);
+        const bool more = s + 1 < steps;
+        if (s + 2 < steps) nxt2 = load_row6<TAIL>(img, g, x, ys + dir * (s + 4), z, m);
 
         // box: horizontal 5-sums of the vertical sums, columns 4k..4k+3
         uint32_t AE[5], AO[5];  // AE[k+1] = (hi VE[k], lo VE[k+1]), k = -1..3
@@ -156,10 +160,11 @@ __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uin
                     (box1(ho >> 16) << 24);
         }
         const int64_t row = (int64_t)z * g.pz + (int64_t)y * g.py;
-        if (!TAIL || nv == 16) {
+        const bool own = P == 64 || s < n;
+        if (!TAIL || (own && nv == 16)) {
             u32x4 vb = {bo[0], bo[1], bo[2], bo[3]};
             __builtin_nontemporal_store(vb, reinterpret_cast<u32x4*>(box + row + x));
-        } else if (nv > 0) {
+        } else if (own && nv > 0) {
             uint8_t* p = box + row + x;
             if (nv & 8) *reinterpret_cast<u32x2*>(p) = u32x2{bo[0], bo[1]};
             const uint32_t w0 = (nv & 8) ? bo[2] : bo[0], w1 = (nv & 8) ? bo[3] : bo[1];
@@ -197,11 +202,13 @@ __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uin
             lo[2 * k + 1] = pk_sub16(__builtin_amdgcn_perm(lq, le, 0x07060302u), BIAS);
         }
         u32x4 s0, s1;
-        exchange(lo, s0, s1);
-        int16_t* lp = lap + row + xw;  // the wave's segment: 16-byte pieces lane and 64 + lane
+        exchange<P>(lo, s0, s1);
+        int16_t* lp = lap + row + xw;  // the lanes' segment: 16-byte pieces lane and P + lane
         if (TAIL) {
-            store_seg(lp + 8 * lane, s0, max(min(g.nx - xw - 8 * lane, 8), 0));
-            store_seg(lp + 512 + 8 * lane, s1, max(min(g.nx - xw - 512 - 8 * lane, 8), 0));
+            if (own) {
+                store_seg(lp + 8 * lane, s0, max(min(g.nx - xw - 8 * lane, 8), 0));
+                store_seg(lp + 8 * P + 8 * lane, s1, max(min(g.nx - xw - 8 * P - 8 * lane, 8), 0));
+            }
         } else {
             __builtin_nontemporal_store(s0, reinterpret_cast<u32x4*>(lp) + lane);
             __builtin_nontemporal_store(s1, reinterpret_cast<u32x4*>(lp) + 64 + lane);
@@ -221,10 +228,21 @@ __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uin
     }
 }
 
-template <bool LAP8>
+template <bool LAP8, int P>
 __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ img, uint8_t* __restrict__ box,
                                                     int16_t* __restrict__ lap, Geo g, int cy, int gyn, int ntiles) {
-    // launched as waves x chunks: a wave's tile is (x wave, chunk, layer)
+    // launched as waves x chunks: a wave's tile is (x wave, chunk, layer); in
+    // rows of at most 16 P < 1024 pixels, 64 / P tiles (chunk, layer)
+    if constexpr (P < 64) {
+        const int wave = xcd_remap(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+        const int first = wave * (64 / P);
+        if (first >= ntiles) return;
+        const int t = min(first + (int)(threadIdx.x & 63) / P, ntiles - 1);  // (the last wave's spare lanes repeat its last)
+        const int by = t % gyn, z = t / gyn, y0 = by * cy, y1 = min(y0 + cy, g.ny);
+        const int dir = (by & 1) ? -1 : 1;
+        image_march<LAP8, true, P>(img, box, lap, g, 0, z, dir > 0 ? y0 : y1 - 1, dir, y1 - y0, min(cy, g.ny));
+        return;
+    }
     const int nxw = (g.nx + 1023) / 1024;
     const int nw = blockDim.x >> 6;
     const int tile = xcd_remap(blockIdx.x, gridDim.x) * nw + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -236,8 +254,16 @@ __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ 
     const int dir = (by & 1) ? -1 : 1;
     const int ys = dir > 0 ? y0 : y1 - 1;
     // the dword after the wave's last lane lies in the row: no lane needs the edge rule
-    if (xw + 1024 + 4 <= g.nx) image_march<LAP8, false>(img, box, lap, g, xw, z, ys, dir, y1 - y0);
-    else image_march<LAP8, true>(img, box, lap, g, xw, z, ys, dir, y1 - y0);
+    if (xw + 1024 + 4 <= g.nx) image_march<LAP8, false, 64>(img, box, lap, g, xw, z, ys, dir, y1 - y0, y1 - y0);
+    else image_march<LAP8, true, 64>(img, box, lap, g, xw, z, ys, dir, y1 - y0, y1 - y0);
+}
+
+template <int P>
+static void run_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g, bool lap8, int cy, int gyn, int n,
+                      hipStream_t s) {
+    const dim3 grid((unsigned)((n + 256 / P - 1) / (256 / P)));
+    if (lap8) hipLaunchKernelGGL((image_kernel<true, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n);
+    else hipLaunchKernelGGL((image_kernel<false, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n);
 }
 
 hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g,
@@ -247,9 +273,13 @@ hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Ge
     const int gyn = (g.ny + cy - 1) / cy;
     const int64_t n = (int64_t)((g.nx + 1023) / 1024) * gyn * g.nz;
     if (n >= (int64_t)1 << 26) return hipErrorInvalidValue;  // a launch dimension holds under 2^32 threads
-    const dim3 grid((unsigned)((n + 3) / 4));
-    if (lap_kind == 8) hipLaunchKernelGGL(image_kernel<true>, grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, (int)n);
-    else hipLaunchKernelGGL(image_kernel<false>, grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, (int)n);
+    const bool lap8 = lap_kind == 8;
+    switch (image_lanes(g.nx)) {
+        case 8: run_image<8>(img, box, lap, g, lap8, cy, gyn, (int)n, s); break;
+        case 16: run_image<16>(img, box, lap, g, lap8, cy, gyn, (int)n, s); break;
+        case 32: run_image<32>(img, box, lap, g, lap8, cy, gyn, (int)n, s); break;
+        default: run_image<64>(img, box, lap, g, lap8, cy, gyn, (int)n, s); break;
+    }
     return hipGetLastError();
 }
 

@@ -116,6 +116,9 @@ hipError_t launch_reduce_finish(const RedArgs& ra, int n, hipStream_t s);
 hipError_t launch_reduce(const void* a, const void* b, int dtype, const Geo& g, RedArgs ra,
                          hipStream_t s, int max_blocks, int* nblocks);
 
+// Lanes of a wave that the image kernel gives a row of nx pixels, 16 each.
+inline int image_lanes(int64_t nx) { return nx <= 128 ? 8 : nx <= 256 ? 16 : nx <= 512 ? 32 : 64; }
+
 // Integer image filters: box 5x5 (rounded mean) and 3x3 Laplacian.
 // `cy` rows per block (fast kernel).
 hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g,
