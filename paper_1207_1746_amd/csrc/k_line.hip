@@ -2,11 +2,15 @@
 // and the _dec variants).  One thread owns one line and walks it cell by cell
 // in the requested order, so every cell is processed after the previous cell
 // of its line; lines run in parallel.  Lanes map to consecutive x positions
-// for lines along y and z (coalesced accesses at every step); the inputs of
-// the next 8 cells are requested together before the recurrence consumes
-// them, so a line keeps 8 loads per input grid in flight while the
-// sequential part runs from registers.  Lines along x are transposed through
-// LDS (line_x_kernel below).
+// for lines along y and z (coalesced accesses at every step).  Lines along x are
+// transposed through LDS (line_x_kernel below).
+//
+// Lines along y and z: many lines are bound by memory, and each requests the
+// inputs of its next 8 cells together before the recurrence consumes them.  Few
+// lines (under one wave per SIMD) are bound by the latency of one line: it
+// requests 16 cells while it consumes the 16 before, and the lines go out in
+// blocks of one wave, over as many CUs as there are (2 x 1377 x 509, elimination
+// along y, FP32: 253 -> 149 us).
 #include "launch.h"
 
 namespace gk {
@@ -38,54 +42,74 @@ __device__ __forceinline__ void line_cell(const T (&v)[KIND == LINE_TRIDIAG_FWD 
     }
 }
 
-template <class T, int KIND, int AXIS>
+// U cells requested together; AHEAD: while the U before them are consumed.
+template <class T, int KIND, int AXIS, int U, bool AHEAD>
 __global__ __launch_bounds__(256) void line_kernel(LineArgs a) {
-#pragma clang fp contract(off)
     constexpr int NI = KIND == LINE_TRIDIAG_FWD ? 4 : 2;
-    constexpr int U = 8;
     int64_t np, nq;
     int len;
     if (AXIS == 2) { len = a.nz; np = a.nx; nq = a.ny; }
-    else if (AXIS == 1) { len = a.ny; np = a.nx; nq = a.nz; }
-    else { len = a.nx; np = a.ny; nq = a.nz; }
+    else { len = a.ny; np = a.nx; nq = a.nz; }
     const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= np * nq) return;
     const int64_t p = l % np, q = l / np;
-    int64_t off0, stride;
-    if (AXIS == 2) { off0 = q * a.py + p; stride = a.pz; }
-    else if (AXIS == 1) { off0 = q * a.pz + p; stride = a.py; }
-    else { off0 = q * a.pz + p * a.py; stride = 1; }
-    const int dir = a.dir;
-    auto at = [&](int s) -> int64_t { return off0 + (int64_t)(dir > 0 ? s : len - 1 - s) * stride; };
+    const int64_t step = (AXIS == 2 ? a.pz : a.py) * a.dir;
+    const int64_t off0 = (AXIS == 2 ? q * a.py : q * a.pz) + p + (a.dir > 0 ? 0 : (len - 1) * -step);
 
     const T* in[NI];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) in[i] = static_cast<const T*>(a.in[i]);
-    T* out0 = static_cast<T*>(a.out[0]);
-    T* out1 = static_cast<T*>(a.out[1]);
+    for (int i = 0; i < NI; ++i) in[i] = static_cast<const T*>(a.in[i]) + off0;
+    T* out0 = static_cast<T*>(a.out[0]) + off0;
+    T* out1 = KIND == LINE_TRIDIAG_FWD ? static_cast<T*>(a.out[1]) + off0 : nullptr;
 
     T s0 = KIND == LINE_RECUR ? (T)a.seed : T(0), s1 = T(0);
-    for (int s = 0; s < len; s += U) {
-        T v[NI][U];
+    auto fetch = [&](int s, T (&v)[U][NI]) __attribute__((always_inline)) {
+        // (past the end: the last cell again)
+        const int64_t last = (int64_t)(len - 1) * step;
+        const bool whole = s + U <= len;
+        int64_t o = s < len ? s * step : last;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s + u < len) {
-                const int64_t o = at(s + u);
 #pragma unroll
-                for (int i = 0; i < NI; ++i) v[i][u] = in[i][o];
-            }
+            for (int i = 0; i < NI; ++i) v[u][i] = in[i][o];
+            o = whole || s + u + 1 < len ? o + step : last;
         }
+    };
+    int64_t oc = 0;  // offset of the next cell
+    auto cell = [&](const T (&v)[NI]) __attribute__((always_inline)) {
+        T r[2];
+        line_cell<T, KIND>(v, s0, s1, r);
+        out0[oc] = r[0];
+        if (KIND == LINE_TRIDIAG_FWD) out1[oc] = r[1];
+        oc += step;
+    };
+    auto cells = [&](int s, const T (&v)[U][NI]) __attribute__((always_inline)) {
+        if (s + U <= len) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (s + u < len) {
-                const int64_t o = at(s + u);
-                T vi[NI], r[2];
+            for (int u = 0; u < U; ++u) cell(v[u]);
+        } else {
 #pragma unroll
-                for (int i = 0; i < NI; ++i) vi[i] = v[i][u];
-                line_cell<T, KIND>(vi, s0, s1, r);
-                out0[o] = r[0];
-                if (KIND == LINE_TRIDIAG_FWD) out1[o] = r[1];
-            }
+            for (int u = 0; u < U; ++u)
+                if (s + u < len) cell(v[u]);
+        }
+    };
+    T v[U][NI];
+    fetch(0, v);
+    if (AHEAD) {
+        T w[U][NI];
+        for (int s = 0; s < len; s += 2 * U) {
+            fetch(s + U, w);
+            cells(s, v);
+            if (s + U >= len) break;
+            fetch(s + 2 * U, v);
+            cells(s + U, w);
+        }
+    } else {
+        for (int s = 0;;) {
+            cells(s, v);
+            s += U;
+            if (s >= len) break;
+            fetch(s, v);
         }
     }
 }
@@ -100,7 +124,7 @@ __global__ __launch_bounds__(256) void line_kernel(LineArgs a) {
 // inputs are requested before the current one is walked.  Rows are padded by
 // one element in LDS so the per-line walk (lanes on different rows, same
 // column) spreads over the banks.
-template <class T, int KIND, int CH, int LX>
+template <class T, int KIND, int CH, int LX, bool REV>
 __global__ __launch_bounds__(LX) void line_x_kernel(LineArgs a) {
     constexpr int NI = KIND == LINE_TRIDIAG_FWD ? 4 : 2;
     constexpr int NO = KIND == LINE_TRIDIAG_FWD ? 2 : 1;
@@ -111,7 +135,9 @@ __global__ __launch_bounds__(LX) void line_x_kernel(LineArgs a) {
     const int t = threadIdx.x;
     const int64_t nl = (int64_t)a.ny * a.nz;
     const int64_t l0 = (int64_t)blockIdx.x * LX;
-    const int nx = a.nx, dir = a.dir;
+    const int nx = a.nx;
+    // (the elimination, short of registers, takes its direction at run time)
+    const bool rev = KIND == LINE_TRIDIAG_FWD ? a.dir < 0 : REV;
     // cooperative accesses: this thread's column within the chunk, and the
     // rows it touches (t / CH + j * RPJ for j < CH)
     const int col = t % CH, r0 = t / CH;
@@ -125,7 +151,7 @@ __global__ __launch_bounds__(LX) void line_x_kernel(LineArgs a) {
     T s0 = KIND == LINE_RECUR ? (T)a.seed : T(0), s1 = T(0);
     const int nchunks = (nx + CH - 1) / CH;
     // cells [x0, x0 + CH) of chunk q in x order; the walk visits them in the line's order
-    auto chunk_x0 = [&](int q) { return dir > 0 ? q * CH : nx - (q + 1) * CH; };
+    auto chunk_x0 = [&](int q) { return rev ? nx - (q + 1) * CH : q * CH; };
     // offsets of the rows this thread loads and stores (-1: past the last line)
     int64_t rb[CH];
 #pragma unroll
@@ -160,17 +186,28 @@ __global__ __launch_bounds__(LX) void line_x_kernel(LineArgs a) {
         __syncthreads();
         if (q + 1 < nchunks) fetch(q + 1);
         if (live) {
+            // eight cells at a time, their inputs read together: the walk waits for
+            // LDS once per eight cells (the elimination's four inputs have no
+            // registers for that beside the next chunk's)
+            constexpr int W = KIND == LINE_TRIDIAG_FWD ? 1 : 8, UNROLL = KIND == LINE_TRIDIAG_FWD ? CH : 1;
+#pragma unroll UNROLL
+            for (int g = 0; g < CH; g += W) {
+                T v[W][NI];
 #pragma unroll
-            for (int cc = 0; cc < CH; ++cc) {
-                const int c = dir > 0 ? cc : CH - 1 - cc;
-                const int xc = x0 + c;
-                if (xc < 0 || xc >= nx) continue;  // ragged last chunk (same for every thread)
-                T v[NI], o[2];
+                for (int u = 0; u < W; ++u) {
+                    const int c = rev ? CH - 1 - (g + u) : g + u;
 #pragma unroll
-                for (int i = 0; i < NI; ++i) v[i] = tile[i][t * PAD + c];
-                line_cell<T, KIND>(v, s0, s1, o);
+                    for (int i = 0; i < NI; ++i) v[u][i] = tile[i][t * PAD + c];
+                }
 #pragma unroll
-                for (int i = 0; i < NO; ++i) tile[i][t * PAD + c] = o[i];
+                for (int u = 0; u < W; ++u) {
+                    const int c = rev ? CH - 1 - (g + u) : g + u;
+                    if (x0 + c < 0 || x0 + c >= nx) continue;  // ragged last chunk (same for every thread)
+                    T o[2];
+                    line_cell<T, KIND>(v[u], s0, s1, o);
+#pragma unroll
+                    for (int i = 0; i < NO; ++i) tile[i][t * PAD + c] = o[i];
+                }
             }
         }
         __syncthreads();
@@ -187,6 +224,14 @@ __global__ __launch_bounds__(LX) void line_x_kernel(LineArgs a) {
     }
 }
 
+template <class T, int KIND, int LX>
+static hipError_t run_line_x(LineArgs& a, int64_t n, hipStream_t s) {
+    const dim3 grid((unsigned)((n + LX - 1) / LX)), blk(LX);
+    if (a.dir > 0 || KIND == LINE_TRIDIAG_FWD) hipLaunchKernelGGL((line_x_kernel<T, KIND, 32, LX, false>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((line_x_kernel<T, KIND, 32, LX, KIND != LINE_TRIDIAG_FWD>), grid, blk, 0, s, a);
+    return hipGetLastError();
+}
+
 template <class T, int KIND>
 static hipError_t run_line(LineArgs& a, int axis, hipStream_t s) {
     int64_t n;
@@ -194,19 +239,30 @@ static hipError_t run_line(LineArgs& a, int axis, hipStream_t s) {
     else if (axis == 1) n = (int64_t)a.nx * a.nz;
     else n = (int64_t)a.ny * a.nz;
     if (n == 0 || (axis == 2 ? a.nz : axis == 1 ? a.ny : a.nx) == 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    if (axis == 2) hipLaunchKernelGGL((line_kernel<T, KIND, 2>), dim3(blocks), dim3(256), 0, s, a);
-    else if (axis == 1) hipLaunchKernelGGL((line_kernel<T, KIND, 1>), dim3(blocks), dim3(256), 0, s, a);
-    else {
+    if (axis == 0) {
         // 32-cell chunks: whole 128-byte (FP32) or 256-byte (FP64) row
         // segments (half-line segments made the four-input elimination read
         // and write each line two to four times; FP64 16-cell chunks ran
         // 2-8% slower); 128 lines per block, 256 for the FP32 recurrence and
-        // substitution, whose LDS tile is smallest (measured)
-        constexpr int CH = 32, LX = (sizeof(T) == 8 || KIND == LINE_TRIDIAG_FWD) ? 128 : 256;
-        const unsigned xb = (unsigned)((n + LX - 1) / LX);
-        hipLaunchKernelGGL((line_x_kernel<T, KIND, CH, LX>), dim3(xb), dim3(LX), 0, s, a);
+        // substitution, whose LDS tile is smallest (measured); 32 where that
+        // would leave CUs without a block (3600 lines of 300 cells, FP64
+        // recurrence: 52 -> 46 us; the elimination is slower so, 98 -> 103)
+        constexpr int LX = (sizeof(T) == 8 || KIND == LINE_TRIDIAG_FWD) ? 128 : 256;
+        if constexpr (KIND != LINE_TRIDIAG_FWD) {
+            if (n < 256 * LX) return run_line_x<T, KIND, 32>(a, n, s);
+        }
+        return run_line_x<T, KIND, LX>(a, n, s);
     }
+    // under one wave per SIMD
+    if (n < 65536) {
+        const dim3 grid((unsigned)((n + 63) / 64)), blk(64);
+        if (axis == 2) hipLaunchKernelGGL((line_kernel<T, KIND, 2, 16, true>), grid, blk, 0, s, a);
+        else hipLaunchKernelGGL((line_kernel<T, KIND, 1, 16, true>), grid, blk, 0, s, a);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
+    if (axis == 2) hipLaunchKernelGGL((line_kernel<T, KIND, 2, 8, false>), grid, blk, 0, s, a);
+    else hipLaunchKernelGGL((line_kernel<T, KIND, 1, 8, false>), grid, blk, 0, s, a);
     return hipGetLastError();
 }
 
