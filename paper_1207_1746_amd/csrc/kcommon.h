@@ -137,24 +137,15 @@ struct Geo {
 
 __device__ __forceinline__ int wrap_idx(int i, int n, int bc) {
     if (bc == BC_PERIODIC) {
-        int m = i % n;
-        return m < 0 ? m + n : m;
+        // one period away unless the extent is shorter than a halo or a tile
+        i = i < 0 ? i + n : (i >= n ? i - n : i);
+        if ((unsigned)i >= (unsigned)n) {
+            i %= n;
+            i = i < 0 ? i + n : i;
+        }
+        return i;
     }
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
-}
-
-// Value at (x, y, z) with the boundary rule applied outside the interior.
-// For 2D layered grids pass the layer as z and keep it in range.
-template <class T, class S>
-__device__ __forceinline__ T fetch_bc(const S* base, const Geo& g, int x, int y, int z) {
-    if ((unsigned)x < (unsigned)g.nx && (unsigned)y < (unsigned)g.ny &&
-        (unsigned)z < (unsigned)g.nz)
-        return from_s<T>(base[(int64_t)z * g.pz + (int64_t)y * g.py + x]);
-    if (g.bc == BC_DIRICHLET) return (T)g.bcv;
-    x = wrap_idx(x, g.nx, g.bc);
-    y = wrap_idx(y, g.ny, g.bc);
-    z = wrap_idx(z, g.nz, g.bc);
-    return from_s<T>(base[(int64_t)z * g.pz + (int64_t)y * g.py + x]);
 }
 
 // ---- XCD-aware block order ----------------------------------------------
