@@ -289,11 +289,11 @@ int gscl_do_all(gscl_ctx *ctx, const gscl_stencil_desc *op, gscl_grid *const *in
 /* Allocation-free do_all, for callers that cannot allocate device memory
  * (code under HIP graph capture, serving loops, harnesses that forbid it).
  * Same operators, arguments, validation, kernels and results as gscl_do_all
- * (bit for bit); a fused reduction keeps its block partials and its result
- * slot in a fixed device array of the library (GSCL_NOALLOC_PARTIALS partials
- * + 64 slots, ~0.5 MB, held on each device the library runs on until the
- * process ends) instead of the context's buffers, and the call never calls
- * hipMalloc or hipFree.  A fused reduction over more blocks than
+ * (bit for bit); a fused reduction keeps its block partials in a fixed device
+ * array of the library (GSCL_NOALLOC_PARTIALS partials, ~0.5 MB, held on each
+ * device the library runs on until the process ends) instead of the context's
+ * buffer, a result for the host goes through the context's pinned slot, and
+ * the call never calls hipMalloc or hipFree.  A fused reduction over more blocks than
  * GSCL_NOALLOC_PARTIALS returns GSCL_ERR_NOMEM (gscl_do_all serves it).
  * Every call on one device shares that array: calls that overlap on one
  * device (several streams, threads or contexts) race and must be ordered by
@@ -372,12 +372,11 @@ typedef struct {
     int32_t inner_sweeps;       /* IR: low-precision sweeps per outer step */
     int32_t kind;               /* GSCL_K_WJACOBI (Poisson, Lap_h u = f),
                                    GSCL_K_RBGS (Poisson by red-black Gauss-Seidel /
-                                   SOR, F64: colour passes in place, or on grids of
-                                   72^3 points or more with planes under 4 GiB
-                                   GSCL_K_RBGS_TB passes of up
-                                   to 4 colour passes through a workspace grid; the
-                                   check follows each chunk as a separate residual
-                                   pass), or
+                                   SOR, F64: GSCL_K_RBGS_TB passes of up to 4
+                                   colour passes through a workspace grid, or on
+                                   planes of 4 GiB and more, or with the least
+                                   workspace, colour passes in place; the check
+                                   follows each chunk as a separate pass), or
                                    GSCL_K_VC13_APPLY (A x = b, several fields) */
     int64_t max_sweeps;
 } gscl_solve_desc;

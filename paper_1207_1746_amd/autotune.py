@@ -41,7 +41,7 @@ def candidates(kind: int, dtype: int, nz: int) -> list[tuple[int, int, int]]:
     if kind == G.K_IMG_BOX5_LAP:
         return [(4, 4, cy) for cy in (4, 8, 16, 32, 64)]
     if kind in BLOCKED:
-        # fixed 16-wave block shape: only the z chunk (output planes) varies
+        # fixed block shape: only the z chunk (output planes) varies
         return [(1, 16, cz) for cz in (1, 2, 4, 8, 16, 32, 64) if cz <= max(nz, 1)]
     if kind in RADIUS2:
         # one-field operators run NW = 4 only; shapes without a kernel are

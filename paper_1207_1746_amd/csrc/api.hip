@@ -422,7 +422,6 @@ static int check_dtypes(gscl_grid* const* g, int first, int count, int dt, const
 // (fixed == nullptr) or the library's fixed device scratch.
 struct FixedScratch {
     double* partials;  // GSCL_NOALLOC_PARTIALS block partials
-    double* result;    // one result slot
 };
 
 static int take_partials(gscl_ctx* c, const FixedScratch* fx, int64_t nblocks) {
@@ -864,7 +863,7 @@ extern "C" int gscl_do_all_noalloc(gscl_ctx* c, const gscl_stencil_desc* op, gsc
         return gscl_fail(GSCL_ERR_STATE, "do_all outside gscl_begin/gscl_end (context state %d)", c->state);
     double* base = scratch_of(c->device);
     if (!base) return gscl_fail(GSCL_ERR_STATE, "fixed scratch of device %d is not set up", c->device);
-    const FixedScratch fx{base, base + GSCL_NOALLOC_PARTIALS};
+    const FixedScratch fx{base};
     return do_all_impl(c, op, in, n_in, out, n_out, fused, fused_result, &fx);
 }
 

@@ -29,7 +29,8 @@
 //   pass starts with the red points), ping-ponging through a second F64
 //   grid (the wide-ghost-zone tiles of the blocked driver, bitwise the same
 //   results): each slot then also has a blocked tile range, walked by a
-//   persistent kernel of 16-wave blocks.
+//   persistent kernel; the z chunk of passes without a reduction is balanced
+//   over the CUs for the whole batch.
 #include <math.h>
 #include <string.h>
 
