@@ -20,10 +20,10 @@
 //     (no stored halo, no halo-fill pass): a lane's columns, the wave's rows
 //     and each plane are wrapped or clamped once, every access reads inside
 //     the grid, and Dirichlet values are selected when a prefetched plane is
-//     taken up.  (Every lane past a row's end used to form its elements from
+//     taken up, after the next one is requested.  (Every lane past a row's end used to form its elements from
 //     their indices, with a division each: 390 x 330 x 350 clamped Jacobi FP32
-//     324 -> 214 us a sweep, 24 x 26 x 181 periodic VARCOEF7 FP32 9.9 -> 7.1,
-//     256^3 142 -> 139.)
+//     324 -> 200 us a sweep, 24 x 26 x 181 periodic VARCOEF7 FP32 9.9 -> 6.9,
+//     256^3 142 -> 138.)
 //   * an optional fused reduction of a per-point value (Section 5.2 fuse) is
 //     accumulated in FP64 registers; block partials are folded by a finish
 //     kernel.
@@ -132,12 +132,14 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
     const bool inside = gx + V <= g.nx, fast = inside || gx >= g.nx + R;
     const int cx = inside ? gx : 0;
     int xi[V];
-    uint64_t km[V];  // lane masks: the element is a value of the grid
+    uint64_t km[V];        // lane masks: the element is a value of the grid
+    bool x_full = true;    // it is in every lane
 #pragma unroll
     for (int i = 0; i < V; ++i) {
         const bool in = gx + i < g.nx, near = gx + i < g.nx + R;
         xi[i] = in ? gx + i : (near ? wrap_idx(gx + i, g.nx, rule) : g.nx - 1);
         km[i] = __ballot(in || !dir);
+        x_full = x_full && km[i] == ~0ull;
     }
     int xhc[R];
     uint64_t xhm[R];
@@ -173,6 +175,7 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
     };
     auto bound_core = [&](int z, T (&o)[V]) __attribute__((always_inline)) {
         const bool ok = yc_ok && z_ok(z);
+        if (ok && x_full) return;  // (the same for the whole wave)
 #pragma unroll
         for (int i = 0; i < V; ++i) o[i] = bound(o[i], ok, km[i]);
     };
@@ -193,6 +196,7 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
         for (int f = 0; f < NF; ++f) {
 #pragma unroll
             for (int r = 0; r < R; ++r) xo[f][r] = bound(xo[f][r], zo && yc_ok, xhm[r]);
+            if (!has_halo_row || (zo && yh_ok && x_full)) continue;
 #pragma unroll
             for (int i = 0; i < V; ++i) yo[f][i] = bound(yo[f][i], zo && yh_ok, km[i]);
         }
@@ -216,10 +220,9 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
         load_point(z0, pa, pb);
     }
 #pragma unroll
-    for (int s = 0; s < (PF ? QD : QD - 1); ++s)
+    for (int s = 0; s < QD - 1; ++s)
 #pragma unroll
         for (int f = 0; f < NF; ++f) bound_core(z0 - RZ + s, q[f][s]);
-    if (PF) bound_halo(z0, xh, yh);
 
     const bool row_ok = gy < g.ny;
 
@@ -238,6 +241,12 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
                 load_core(f, z + RZ, q[f][QD - 1]);
             load_halo(z, xh, yh);
             load_point(z, pa, pb);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) bound_core(z + RZ, q[f][QD - 1]);
+            bound_halo(z, xh, yh);
+        }
+        if (PF) {
+            // the planes requested a step ago, once the next ones are on their way
 #pragma unroll
             for (int f = 0; f < NF; ++f) bound_core(z + RZ, q[f][QD - 1]);
             bound_halo(z, xh, yh);
@@ -356,10 +365,8 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
 #pragma unroll
                     for (int v = 0; v < V; ++v) q[f][s][v] = q[f][s + 1][v];
         } else if (more) {
-            bound_halo(z + 1, xhn, yhn);
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                bound_core(z + RZ + 1, qn[f]);
 #pragma unroll
                 for (int s = 0; s + 1 < QD; ++s)
 #pragma unroll
