@@ -290,11 +290,13 @@ int gscl_do_all(gscl_ctx *ctx, const gscl_stencil_desc *op, gscl_grid *const *in
  * (code under HIP graph capture, serving loops, harnesses that forbid it).
  * Same operators, arguments, validation, kernels and results as gscl_do_all
  * (bit for bit); a fused reduction keeps its block partials in a fixed device
- * array of the library (GSCL_NOALLOC_PARTIALS partials, ~0.5 MB, held on each
+ * array of the library (2 * GSCL_NOALLOC_PARTIALS doubles, 1 MB, held on each
  * device the library runs on until the process ends) instead of the context's
  * buffer, a result for the host goes through the context's pinned slot, and
  * the call never calls hipMalloc or hipFree.  A fused reduction over more blocks than
- * GSCL_NOALLOC_PARTIALS returns GSCL_ERR_NOMEM (gscl_do_all serves it).
+ * GSCL_NOALLOC_PARTIALS returns GSCL_ERR_NOMEM (gscl_do_all serves it); blocked
+ * passes of k levels are counted as tiles of (64 - 2 k) x (32 - 2 k) points in
+ * chunks of the planes that gscl_tile_get reports.
  * Every call on one device shares that array: calls that overlap on one
  * device (several streams, threads or contexts) race and must be ordered by
  * the caller.  Nothing in the array needs clearing between calls. */

@@ -162,11 +162,13 @@ int ensure_partials(gscl_ctx* c, int64_t nblocks) {
 }
 
 // Fixed device scratch of the allocation-free do_all variant: block partials
-// of a fused reduction followed by one result slot.  Every kernel writes each
-// partial it later folds, so nothing has to start at zero.  Host code never
-// passes the symbol itself: its device address is looked up once per device
-// (with that device current) and kept below.
-static __device__ __align__(256) double scratch[GSCL_NOALLOC_PARTIALS + 64];
+// of a fused reduction, twice the limit that calls are held against because a
+// blocked pass within it may launch up to twice as many blocks
+// (tb_nominal_blocks).  Every kernel writes each partial it later folds, so
+// nothing has to start at zero.  Host code never passes the symbol itself: its
+// device address is looked up once per device (with that device current) and
+// kept below.
+static __device__ __align__(256) double scratch[2 * GSCL_NOALLOC_PARTIALS];
 static std::mutex g_scratch_mu;
 static double* g_scratch_dev[64];
 
@@ -421,7 +423,7 @@ static int check_dtypes(gscl_grid* const* g, int first, int count, int dt, const
 // Where a call's reduction scratch lives: the context's growable buffers
 // (fixed == nullptr) or the library's fixed device scratch.
 struct FixedScratch {
-    double* partials;  // GSCL_NOALLOC_PARTIALS block partials
+    double* partials;  // 2 * GSCL_NOALLOC_PARTIALS block partials
 };
 
 static int take_partials(gscl_ctx* c, const FixedScratch* fx, int64_t nblocks) {
@@ -434,34 +436,17 @@ static int take_partials(gscl_ctx* c, const FixedScratch* fx, int64_t nblocks) {
     return GSCL_OK;
 }
 
-// z chunk of a blocked pass: the one set for these extents, else the one that
-// balances the blocks over the chip.  A fused reduction takes a partial per
-// block: the choice never needs more than the nominal chunk does or 2048, and
-// a call into the fixed scratch is refused by the count its limit has always
-// been held against, that of nominal chunks of tiles with exactly k ghost
-// columns.
+// z chunk of a blocked pass and, for a fused reduction, its partials.
 static int tb_chunk(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d, const gk::Geo& g, int k) {
-    const bool rb = kind == GSCL_K_RBGS_TB, pairs = gk::tb_pairs(dtype == GSCL_F64, rb);
-    const int nominal = pick_tile(c, kind, dtype, d).cz;
-    if (c->tiles.count(std::make_tuple(kind, dtype, d.n[0], d.n[1], d.n[2]))) return nominal;
-    const int64_t most = std::max<int64_t>(gk::tb_blocks(g, k, nominal, pairs), 2048);
-    const int cz = gk::tb_pick_chunk(g.nz, most, rb, dtype == GSCL_F64, k,
-                                     [&](int q) { return gk::tb_blocks(g, k, q, pairs); });
-    return cz ? cz : nominal;
+    const bool set = c->tiles.count(std::make_tuple(kind, dtype, d.n[0], d.n[1], d.n[2]));
+    return gk::tb_launch_chunk(g, k, pick_tile(c, kind, dtype, d).cz, set, kind == GSCL_K_RBGS_TB, dtype == GSCL_F64);
 }
 
 static int tb_partials(gscl_ctx* c, const FixedScratch* fx, int kind, int dtype, const gscl_grid_desc& d,
-                       const gk::Geo& g, int k, int& cz) {
-    const bool pairs = gk::tb_pairs(dtype == GSCL_F64, kind == GSCL_K_RBGS_TB);
-    if (fx) {
-        const int nominal = pick_tile(c, kind, dtype, d).cz, ox = gk::TB_COLS - 2 * k, oy = gk::TB_ROWS - 2 * k;
-        const int rc = take_partials(c, fx, (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) *
-                                                ((g.nz + nominal - 1) / nominal));
-        if (rc) return rc;
-        while (gk::tb_blocks(g, k, cz, pairs) > GSCL_NOALLOC_PARTIALS) ++cz;  // (a few tiles more at odd k)
-        return GSCL_OK;
-    }
-    return take_partials(c, fx, gk::tb_blocks(g, k, cz, pairs));
+                       const gk::Geo& g, int k, int cz) {
+    // the fixed scratch holds what any admitted launch takes
+    if (fx) return take_partials(c, fx, gk::tb_nominal_blocks(g, k, pick_tile(c, kind, dtype, d).cz));
+    return take_partials(c, fx, gk::tb_blocks(g, k, cz, gk::tb_pairs(dtype == GSCL_F64, kind == GSCL_K_RBGS_TB)));
 }
 
 static void fill_red(gscl_ctx* c, const gscl_reduce_desc* rd, gk::RedArgs& ra, const FixedScratch* fx = nullptr) {

@@ -5,11 +5,6 @@
 
 namespace gk {
 
-int64_t tb_blocks(const Geo& g, int k, int cz, bool pairs) {
-    const int ox = tb_out_x(k, pairs), oy = tb_out_y(k);
-    return (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) * ((g.nz + cz - 1) / cz);
-}
-
 template <class T, bool HAS_F, int K, bool RB>
 static hipError_t run_tb(TBArgs& a, bool red, hipStream_t s, int* nblocks) {
     const int n = (int)tb_blocks(a.g, K, a.cz, tb_pairs(sizeof(T) == 8, RB));

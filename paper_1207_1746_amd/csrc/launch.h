@@ -82,7 +82,6 @@ hipError_t launch_diamond(DiamondArgs& a, int dtype, int kind, hipStream_t s);
 hipError_t launch_wjacobi_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
 // k red-black colour passes per pass (first colour in a.p[3]), Dirichlet rule only.
 hipError_t launch_rbgs_tb(TBArgs& a, int dtype, bool has_f, bool red, hipStream_t s, int* nblocks);
-int64_t tb_blocks(const Geo& g, int k, int cz, bool pairs);
 
 // Generic linear operator (any offsets, per-grid boundary rule).  The terms are
 // ordered by output (the caller's order within one); tend[o] ends output o's.

@@ -124,6 +124,30 @@ inline int tb_pick_chunk(int nz, int64_t max_blocks, bool rb, bool f64, int k, T
     return best;
 }
 
+// Blocks of a pass in chunks of cz planes.
+inline int64_t tb_blocks(const Geo& g, int k, int cz, bool pairs) {
+    const int ox = tb_out_x(k, pairs), oy = tb_out_y(k);
+    return (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy) * ((g.nz + cz - 1) / cz);
+}
+
+// z chunk of a launch: the one set for its extents, else the one that balances
+// the blocks over the chip.  A fused reduction takes a partial per block: the
+// choice never needs more of them than the nominal chunk does or 2048.
+inline int tb_launch_chunk(const Geo& g, int k, int nominal, bool set, bool rb, bool f64) {
+    if (set) return nominal;
+    const bool pairs = tb_pairs(f64, rb);
+    const int cz = tb_pick_chunk(g.nz, std::max<int64_t>(tb_blocks(g, k, nominal, pairs), 2048), rb, f64, k,
+                                 [&](int q) { return tb_blocks(g, k, q, pairs); });
+    return cz ? cz : nominal;
+}
+
+// The count that a fused reduction into fixed scratch of `limit` partials is
+// held against: nominal chunks of tiles with exactly k ghost columns.  A launch
+// whose count is within the limit has at most 2 * limit blocks (and 2048): a
+// pair layout's tiles put out two columns less at odd k, 56 instead of 58 or 60
+// instead of 62, so a row takes at most twice as many.
+inline int64_t tb_nominal_blocks(const Geo& g, int k, int nominal) { return tb_blocks(g, k, nominal, false); }
+
 // Value of the lane below (lane - 1) or above (lane + 1) in the wave, by
 // wave-wide DPP shifts (wave_shr:1 / wave_shl:1); lanes without a source get 0.
 template <int CTRL>
