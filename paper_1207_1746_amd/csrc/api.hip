@@ -516,19 +516,19 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
             la.g = geo_of(g0);
             la.nin = n_in;
             la.nout = n_out;
-            int radius[16] = {0};
+            int64_t radius[16] = {0};
             for (int t = 0; t < op->nterms; ++t) {
                 const gscl_term& tm = op->terms[t];
                 if (tm.grid < 0 || tm.grid >= n_in || tm.out < 0 || tm.out >= n_out || tm.coef < -1 || tm.coef >= n_in)
                     return gscl_fail(GSCL_ERR_ARG, "term %d references a missing grid", t);
                 if (g0->d.ndim == 2 && tm.dz != 0) return gscl_fail(GSCL_ERR_ARG, "term %d: dz must be 0 in 2D", t);
-                const int r = std::max(std::abs(tm.dx), std::max(std::abs(tm.dy), std::abs(tm.dz)));
-                radius[tm.grid] = std::max(radius[tm.grid], r);
+                for (int64_t d : {tm.dx, tm.dy, tm.dz})  // (64 bits: -2^31 has a magnitude too)
+                    radius[tm.grid] = std::max(radius[tm.grid], d < 0 ? -d : d);
             }
             for (int i = 0; i < n_in; ++i) {
                 if (in[i]->d.halo < radius[i])
-                    return gscl_fail(GSCL_ERR_HALO, "input %d is read at offset %d but declares halo %d", i,
-                                     radius[i], in[i]->d.halo);
+                    return gscl_fail(GSCL_ERR_HALO, "input %d is read at offset %lld but declares halo %d", i,
+                                     (long long)radius[i], in[i]->d.halo);
                 if (radius[i] > 0)
                     for (int o = 0; o < n_out; ++o)
                         if (overlaps(in[i], out[o]))
