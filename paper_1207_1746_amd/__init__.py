@@ -278,10 +278,9 @@ def _handles(grids: Iterable[Grid]):
 def _stencil(kind: int, p: Sequence[float]) -> StencilDesc:
     sd = StencilDesc()
     sd.kind = kind
-    if p:
-        a = sd.p
-        for i, v in enumerate(p):
-            a[i] = float(v)
+    a = sd.p
+    for i, v in enumerate(p):  # (any iterable: an array has no truth value)
+        a[i] = float(v)
     return sd
 
 
