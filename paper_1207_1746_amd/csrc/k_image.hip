@@ -230,11 +230,15 @@ __device__ __forceinline__ void image_march(const uint8_t* __restrict__ img, uin
 
 template <bool LAP8, int P>
 __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ img, uint8_t* __restrict__ box,
-                                                    int16_t* __restrict__ lap, Geo g, int cy, int gyn, int ntiles) {
+                                                    int16_t* __restrict__ lap, Geo g, int cy, int gyn, int ntiles,
+                                                    int nblocks) {
+    const int id = blockIdx.y * gridDim.x + blockIdx.x;
+    if (id >= nblocks) return;
+    const int block = xcd_remap(id, nblocks);
     // launched as waves x chunks: a wave's tile is (x wave, chunk, layer); in
     // rows of at most 16 P < 1024 pixels, 64 / P tiles (chunk, layer)
     if constexpr (P < 64) {
-        const int wave = xcd_remap(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+        const int wave = block * (blockDim.x >> 6) + (threadIdx.x >> 6);
         const int first = wave * (64 / P);
         if (first >= ntiles) return;
         const int t = min(first + (int)(threadIdx.x & 63) / P, ntiles - 1);  // (the last wave's spare lanes repeat its last)
@@ -245,7 +249,7 @@ __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ 
     }
     const int nxw = (g.nx + 1023) / 1024;
     const int nw = blockDim.x >> 6;
-    const int tile = xcd_remap(blockIdx.x, gridDim.x) * nw + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = block * nw + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tile >= ntiles) return;
     const int xw = (tile % nxw) * 1024, by = (tile / nxw) % gyn, z = tile / (nxw * gyn);
     const int y0 = by * cy, y1 = min(y0 + cy, g.ny);
@@ -261,18 +265,25 @@ __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ 
 template <int P>
 static void run_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g, bool lap8, int cy, int gyn, int n,
                       hipStream_t s) {
-    const dim3 grid((unsigned)((n + 256 / P - 1) / (256 / P)));
-    if (lap8) hipLaunchKernelGGL((image_kernel<true, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n);
-    else hipLaunchKernelGGL((image_kernel<false, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n);
+    const int nb = (n + 256 / P - 1) / (256 / P);
+    // a launch dimension holds under 2^32 threads
+    constexpr int GX = 1 << 20;
+    const dim3 grid((unsigned)std::min(nb, GX), (unsigned)((nb + GX - 1) / GX));
+    if (lap8) hipLaunchKernelGGL((image_kernel<true, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n, nb);
+    else hipLaunchKernelGGL((image_kernel<false, P>), grid, dim3(256), 0, s, img, box, lap, g, cy, gyn, n, nb);
 }
 
 hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g,
                         int lap_kind, int cy, hipStream_t s) {
     if (g.nx == 0 || g.ny == 0 || g.nz == 0) return hipSuccess;
     if (cy < 1) cy = 32;
+    cy = std::min(cy, g.ny);
+    auto tiles = [&] { return (int64_t)((g.nx + 1023) / 1024) * ((g.ny + cy - 1) / cy) * g.nz; };
+    // tile indices are 32-bit: longer chunks of rows where there are too many
+    while (tiles() > (int64_t)1 << 30 && cy < g.ny) cy = (int)std::min<int64_t>(2 * (int64_t)cy, g.ny);
     const int gyn = (g.ny + cy - 1) / cy;
-    const int64_t n = (int64_t)((g.nx + 1023) / 1024) * gyn * g.nz;
-    if (n >= (int64_t)1 << 26) return hipErrorInvalidValue;  // a launch dimension holds under 2^32 threads
+    const int64_t n = tiles();
+    if (n > (int64_t)1 << 30) return hipErrorInvalidValue;
     const bool lap8 = lap_kind == 8;
     switch (image_lanes(g.nx)) {
         case 8: run_image<8>(img, box, lap, g, lap8, cy, gyn, (int)n, s); break;
