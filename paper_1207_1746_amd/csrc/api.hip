@@ -739,9 +739,11 @@ static int do_all_impl(gscl_ctx* c, const gscl_stencil_desc* op, gscl_grid* cons
             const int lk = (int)op->p[0];
             if (lk != 4 && lk != 8) return gscl_fail(GSCL_ERR_ARG, "Laplacian kind p[0] must be 4 or 8");
             if (red) return gscl_fail(GSCL_ERR_UNSUPPORTED, "IMG_BOX5_LAP has no fused reduction");
-            gk::TileCfg t = pick_tile(c, op->kind, dt, g0->d);
-            he = gk::launch_image((const uint8_t*)g0->ptr, (uint8_t*)out[0]->ptr, (int16_t*)out[1]->ptr, geo_of(g0),
-                                  lk, t.cz, c->stream);
+            const gk::Geo g = geo_of(g0);
+            const bool set = c->tiles.count(std::make_tuple((int)op->kind, dt, g0->d.n[0], g0->d.n[1], g0->d.n[2]));
+            const int cy = !set && gk::image_by_pixel(g) ? 0 : pick_tile(c, op->kind, dt, g0->d).cz;
+            he = gk::launch_image((const uint8_t*)g0->ptr, (uint8_t*)out[0]->ptr, (int16_t*)out[1]->ptr, g, lk, cy,
+                                  c->stream);
             break;
         }
         case GSCL_K_VC13_APPLY:

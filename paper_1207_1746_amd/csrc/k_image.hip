@@ -26,7 +26,8 @@
 // rows, each on as many lanes as its row needs (4 x 137 x 4145: 18.9 us with a
 // row per wave, 16.7 with a thread per pixel, 9.7 so).  8 x 1918 x 1078, 8-neighbour Laplacian: 76.7 -> 20.5 us
 // (before, widths that are not a multiple of 16 and the 8-neighbour Laplacian
-// ran one thread per pixel with 25 byte loads).
+// ran one thread per pixel with 25 byte loads).  Small images still do: see
+// image_by_pixel.
 #include "launch.h"
 
 namespace gk {
@@ -262,6 +263,38 @@ __global__ __launch_bounds__(256) void image_kernel(const uint8_t* __restrict__ 
     else image_march<LAP8, true, 64>(img, box, lap, g, xw, z, ys, dir, y1 - y0, y1 - y0);
 }
 
+// One thread per pixel, 25 byte loads each, all in flight together: the chain
+// of a small image is one load's latency, where a march's is its first five
+// rows, the filters of 16 pixels and an exchange of lanes.
+__global__ __launch_bounds__(256) void image_pixels(const uint8_t* __restrict__ img, uint8_t* __restrict__ box,
+                                                    int16_t* __restrict__ lap, Geo g, int lap_kind) {
+    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int z = blockIdx.z;
+    if (x >= g.nx || y >= g.ny) return;
+    const uint8_t* pl = img + (int64_t)z * g.pz;
+    auto at = [&](int xx, int yy) -> int {
+        xx = xx < 0 ? 0 : (xx >= g.nx ? g.nx - 1 : xx);
+        yy = yy < 0 ? 0 : (yy >= g.ny ? g.ny - 1 : yy);
+        return pl[(int64_t)yy * g.py + xx];
+    };
+    uint32_t s = 0;
+    for (int dy = -2; dy <= 2; ++dy)
+        for (int dx = -2; dx <= 2; ++dx) s += at(x + dx, y + dy);
+    const int c = at(x, y);
+    int l;
+    if (lap_kind == 8) {
+        l = -9 * c;
+        for (int dy = -1; dy <= 1; ++dy)
+            for (int dx = -1; dx <= 1; ++dx) l += at(x + dx, y + dy);
+    } else {
+        l = at(x, y - 1) + at(x, y + 1) + at(x - 1, y) + at(x + 1, y) - 4 * c;
+    }
+    const int64_t off = (int64_t)z * g.pz + (int64_t)y * g.py + x;
+    box[off] = (uint8_t)box1(s);
+    lap[off] = (int16_t)l;
+}
+
 template <int P>
 static void run_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g, bool lap8, int cy, int gyn, int n,
                       hipStream_t s) {
@@ -276,7 +309,11 @@ static void run_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo&
 hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g,
                         int lap_kind, int cy, hipStream_t s) {
     if (g.nx == 0 || g.ny == 0 || g.nz == 0) return hipSuccess;
-    if (cy < 1) cy = 32;
+    if (cy == 0) {
+        const dim3 grid((g.nx + 63) / 64, (g.ny + 3) / 4, g.nz);
+        hipLaunchKernelGGL(image_pixels, grid, dim3(256), 0, s, img, box, lap, g, lap_kind);
+        return hipGetLastError();
+    }
     cy = std::min(cy, g.ny);
     auto tiles = [&] { return (int64_t)((g.nx + 1023) / 1024) * ((g.ny + cy - 1) / cy) * g.nz; };
     // tile indices are 32-bit: longer chunks of rows where there are too many

@@ -118,8 +118,15 @@ hipError_t launch_reduce(const void* a, const void* b, int dtype, const Geo& g, 
 // Lanes of a wave that the image kernel gives a row of nx pixels, 16 each.
 inline int image_lanes(int64_t nx) { return nx <= 128 ? 8 : nx <= 256 ? 16 : nx <= 512 ? 32 : 64; }
 
+// Whether an image whose rows per wave no one has set is filtered by a thread per
+// pixel: up to 640 Ki lanes of rows in whole waves.  us a call in a row of calls
+// (a thread per pixel / 16 pixels per lane; in brackets the kernel alone): 100^2
+// 5.5 / 5.8 (3.0 / 4.2), 2 x 300 x 200 5.5 / 5.8 (3.2 / 4.9), 1340 x 294 5.4 / 5.7
+// (4.6 / 4.6), 1918 x 300 5.5 / 5.8 (5.7 / 4.7), 8000 x 100 5.9 / 5.8.
+inline bool image_by_pixel(const Geo& g) { return ((int64_t)g.nx + 63) / 64 * 64 * g.ny * g.nz <= 5 << 17; }
+
 // Integer image filters: box 5x5 (rounded mean) and 3x3 Laplacian.
-// `cy` rows per block (fast kernel).
+// `cy` rows per wave (0: a thread per pixel).
 hipError_t launch_image(const uint8_t* img, uint8_t* box, int16_t* lap, const Geo& g,
                         int lap_kind, int cy, hipStream_t s);
 
