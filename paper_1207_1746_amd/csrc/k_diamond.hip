@@ -210,11 +210,13 @@ static hipError_t run_tiled(DiamondArgs& a, hipStream_t s) {
 // Tiles of 64 x 32 where a diagonal of them fills the chip: their LDS lets four
 // blocks (FP64 RECUR: three) share a CU where 64 x 64 tiles leave two (one), and
 // blocks that load and store cover those that walk (GS2D FP64, 1024 x 256^2: 581
-// us on 64 x 64, 480 on 64 x 32).  Elsewhere 64 x 64: fewer diagonals.
+// us on 64 x 64, 480 on 64 x 32).  Elsewhere 64 x 64: fewer diagonals; also where
+// a diagonal of 64 x 32 has more threads than a launch dimension holds, 2^32.
 template <class T, int KIND>
 static hipError_t pick_tiles(DiamondArgs& a, hipStream_t s) {
     const int64_t wide = std::min((a.nx + DT - 1) / DT, (a.ny + 31) / 32);
-    return wide * a.nl >= 512 ? run_tiled<T, KIND, 32>(a, s) : run_tiled<T, KIND, 64>(a, s);
+    const int64_t blocks = wide * a.nl;
+    return blocks >= 512 && blocks * (64 * DNW) < (int64_t)1 << 32 ? run_tiled<T, KIND, 32>(a, s) : run_tiled<T, KIND, 64>(a, s);
 }
 
 template <class T>
