@@ -142,6 +142,15 @@ namespace gk {
 // Poisson residual r = f - Lap_h x (F64 math, F32 output) with optional fused
 // sum of squares of r.
 hipError_t launch_poisson_resid(TArgs& a, const TileCfg& c, bool red, hipStream_t s, int* nblocks);
-// Its fused reduction alone: no output grid.
+// Its fused reduction alone: no output grid.  Chunk of z planes: read-only, so
+// short chunks cost little, and 2048 blocks and up keep the loads of every CU in
+// flight (192^3: 29 us, 53 as a residual sweep of 288 blocks that also writes the
+// residual); up to 32 planes, more where that would take over 65536 blocks (thin
+// grids: a launch dimension holds under 2^32 threads).
+inline int norm_chunk(const Geo& g, int V, int NW) {
+    const int64_t planes = ((int64_t)g.nx + 64 * V - 1) / (64 * V) * ((g.ny + NW - 1) / NW) * g.nz;
+    const int64_t cz = std::min<int64_t>(std::max<int64_t>(planes / 2048, 2), 32);
+    return (int)std::max<int64_t>(cz, (planes + 65535) / 65536);
+}
 hipError_t launch_poisson_norm(TArgs& a, const TileCfg& c, hipStream_t s, int* nblocks);
 }  // namespace gk

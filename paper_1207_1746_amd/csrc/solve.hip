@@ -174,9 +174,7 @@ static int run_chunks(gscl_ctx* c, Cleanup& cl, size_t npasses, int S, int64_t m
 }
 
 // ||b - A x||^2 into *result; x and b as the sweeps before it have checked
-// them.  Read-only, so short chunks cost little: 2048 blocks and up keep the
-// loads of every CU in flight (192^3: 53 us as a residual sweep of 288 blocks
-// that also writes the residual).
+// them.
 static int poisson_norm(gscl_ctx* c, const gscl_grid* x, const gscl_grid* b, double h2, double* result) {
     gk::TArgs a;
     memset(&a, 0, sizeof a);
@@ -188,8 +186,7 @@ static int poisson_norm(gscl_ctx* c, const gscl_grid* x, const gscl_grid* b, dou
     gk::TileCfg t;
     t.V = a.g.nx >= 128 ? 2 : 1;
     t.NW = 4;
-    const int64_t cols = ((int64_t)a.g.nx + 64 * t.V - 1) / (64 * t.V) * ((a.g.ny + 3) / 4);
-    t.cz = (int)std::min<int64_t>(std::max<int64_t>(cols * a.g.nz / 2048, 2), 32);
+    t.cz = gk::norm_chunk(a.g, t.V, t.NW);
     int nb = gk::tiled_blocks(a.g, t);
     int rc = ensure_partials(c, nb);
     if (rc) return rc;

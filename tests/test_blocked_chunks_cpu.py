@@ -1,8 +1,12 @@
-"""Host rules of a blocked pass's launch (compiled here for the host alone): the
-z chunk it takes, and the count that decides whether its fused reduction fits
-the fixed scratch of gscl_do_all_noalloc.  Every admitted call has at most as
-many blocks as the scratch holds, around the limit, for every number of levels
-and both layouts, with the chunk picked and with one set."""
+"""Host rules of launches, compiled here for the host alone.
+
+A blocked pass: the z chunk it takes, and the count that decides whether its
+fused reduction fits the fixed scratch of gscl_do_all_noalloc.  Every admitted
+call has at most as many blocks as the scratch holds, around the limit, for
+every number of levels and both layouts, with the chunk picked and with one set.
+
+The norm of a red-black solve's check: its blocks fit one launch dimension and
+the partials of its points, thin grids and the largest among them."""
 import os
 import shutil
 import subprocess
@@ -11,7 +15,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-SOURCE = r"""
+CHUNKS = r"""
 #include <stdio.h>
 #include "gscl.h"
 #include "tb7.h"
@@ -51,15 +55,53 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not (shutil.which("hipcc") or os.path.exists("/opt/rocm/bin/hipcc")), reason="no hipcc")
-def test_admitted_reductions_fit_the_fixed_scratch(tmp_path):
-    src, exe = tmp_path / "chunks.hip", tmp_path / "chunks"
-    src.write_text(SOURCE)
-    subprocess.run([shutil.which("hipcc") or "/opt/rocm/bin/hipcc", "--offload-host-only", "-std=c++17", "-I",
-                    os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1207_1746_amd", "csrc"), str(src),
-                    "-o", str(exe)], check=True, capture_output=True)
+NORM = r"""
+#include <stdio.h>
+#include "launch.h"
+using namespace gk;
+
+int main() {
+    long seen = 0, bad = 0;
+    for (long x : {1L, 3L, 127L, 128L, 192L, 1000L, 1L << 20, 1L << 30})
+        for (long y : {1L, 4L, 5L, 192L, 4097L, 1L << 20, 1L << 30})
+            for (long z : {1L, 2L, 33L, 192L, 5000L, 1L << 20, 1L << 30}) {
+                if (x * y > 1L << 34 || x * y * z > 1L << 34) continue;
+                const Geo g{(int)x, (int)y, (int)z, 0, 0, 0, 0.0};
+                const int V = x >= 128 ? 2 : 1, cz = norm_chunk(g, V, 4);
+                const long cols = (x + 64 * V - 1) / (64 * V) * ((y + 3) / 4), n = cols * ((z + cz - 1) / (long)cz);
+                // partials that a context holds or a solve reserves for its points
+                const long held = x * y * z / 32 + 65 > 65536 ? x * y * z / 32 + 65 : 65536;
+                ++seen;
+                if (cols > held || cols >= 1L << 24) continue;  // one chunk in z cannot be fewer blocks
+                bad += cz < 2 || n >= 1L << 24 || n > held;
+            }
+    printf("%ld %ld\n", seen, bad);
+    return 0;
+}
+"""
+
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+
+def _run(tmp_path, source):
+    src, exe = tmp_path / "rules.hip", tmp_path / "rules"
+    src.write_text(source)
+    subprocess.run([HIPCC, "--offload-host-only", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_1207_1746_amd", "csrc"), str(src), "-o", str(exe)], check=True,
+                   capture_output=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
-    admitted, over, bad = map(int, out.split())
+    return map(int, out.split())
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_admitted_reductions_fit_the_fixed_scratch(tmp_path):
+    admitted, over, bad = _run(tmp_path, CHUNKS)
     assert bad == 0
     # the band that is admitted by its count and launches more blocks than the limit is there
     assert admitted > 1000 and over > 0
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_norm_blocks_fit_a_launch(tmp_path):
+    seen, bad = _run(tmp_path, NORM)
+    assert bad == 0 and seen > 100
