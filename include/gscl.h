@@ -449,12 +449,14 @@ size_t gscl_batch_footprint(const gscl_batch *b, const int64_t n[3]);
  * paper names as future work, Sections 2 and 6): rule i applies to requests
  * whose largest extent is <= edge[i] (the first such i; edges increasing):
  * one-sweep tiles of cz[i] z planes (the residual and plain sweep passes) and
- * blocked-pass tiles of at least tb_cz[i] planes; 0 keeps the built-in
+ * blocked-pass tiles of at least tb_cz[i] planes (of at most tb_cz[i] in
+ * passes that would have fewer than 512 tiles so); 0 keeps the built-in
  * choice, and larger requests use the built-in rule.  Applies to requests
- * admitted after the call (nrules 0 clears the rule).  A request's tiles
- * depend only on its own extents and the rule, so its result is the same
- * alone and among any others under one rule; the blocked passes of
- * refinement batches carry no reduction, so their tb_cz changes no result.
+ * admitted after the call (nrules 0 clears the rule).  The tiles that carry a
+ * request's reductions depend only on its own extents and the rule, so its
+ * result is the same alone and among any others under one rule; blocked
+ * passes without a reduction balance their chunks over the batch, which
+ * changes no result.
  * GSCL_ERR_ARG for more than 64 rules, edges not increasing or chunks
  * outside 0..1024. */
 int gscl_batch_tile_rule(gscl_batch *b, int nrules, const int32_t *edge, const int32_t *cz,

@@ -549,35 +549,21 @@ static void set_tb_tiles(BSlot& s, int kp, bool pairs) {
 }
 
 // Blocked tiles of the passes without a reduction, whose tiling changes no
-// result: one chunk for all slots, chosen like a single launch's; a rule's
-// chunk is kept while the batch has at least 512 tiles with it, and is an upper
-// bound after that (the tail of a stream).
+// result: the slots share one launch.
 static void balance_tb_tiles(gscl_batch* b) {
-    const bool rb = b->desc.method == GSCL_BATCH_RBGS, f64 = b->desc.precision == GSCL_PREC_F64;
-    auto each = [&](auto&& fn) {
-        for (int id = 0; id < b->desc.max_slots; ++id)
-            if (b->used[id]) fn(b->slot[id]);
-    };
-    auto tiles = [&](auto&& chunk) {
-        int64_t n = 0;
-        each([&](BSlot& s) { n += (int64_t)tb_cols(s) * ((s.nz + chunk(s) - 1) / chunk(s)); });
-        return n;
-    };
-    int nzmax = 1;
-    bool ruled = false;
-    each([&](BSlot& s) {
-        nzmax = std::max(nzmax, s.nz);
-        ruled = ruled || s.rule_cz > 0;
-    });
-    const bool keep = ruled && tiles([](const BSlot& s) { return s.rule_cz > 0 ? chunk_of(s, s.rule_cz) : s.rcz; }) >= 512;
-    auto bounded = [&](const BSlot& s, int cz) { return chunk_of(s, s.rule_cz > 0 ? std::min(s.rule_cz, cz) : cz); };
-    const int cz = gk::tb_pick_chunk(nzmax, INT32_MAX, rb, f64, b->desc.sweeps_per_pass,
-                                     [&](int q) { return tiles([&](const BSlot& s) { return bounded(s, q); }); });
-    each([&](BSlot& s) {
-        s.tcz = keep && s.rule_cz > 0 ? chunk_of(s, s.rule_cz) : bounded(s, cz);
+    std::vector<gk::TBShare> share;
+    for (int id = 0; id < b->desc.max_slots; ++id)
+        if (b->used[id]) share.push_back({tb_cols(b->slot[id]), b->slot[id].nz, b->slot[id].rule_cz, 0});
+    gk::tb_share_chunks(share.data(), (int)share.size(), b->desc.method == GSCL_BATCH_RBGS,
+                        b->desc.precision == GSCL_PREC_F64, b->desc.sweeps_per_pass);
+    size_t i = 0;
+    for (int id = 0; id < b->desc.max_slots; ++id) {
+        if (!b->used[id]) continue;
+        BSlot& s = b->slot[id];
+        s.tcz = share[i++].cz;
         s.tncz = (s.nz + s.tcz - 1) / s.tcz;
         s.tb_ntiles = tb_cols(s) * s.tncz;
-    });
+    }
 }
 
 static int upload_table(gscl_batch* b) {

@@ -5,6 +5,9 @@ fused reduction fits the fixed scratch of gscl_do_all_noalloc.  Every admitted
 call has at most as many blocks as the scratch holds, around the limit, for
 every number of levels and both layouts, with the chunk picked and with one set.
 
+Chunks of grids that share a launch: on a full chip the chunk without a rule or
+the rule's, whichever is longer; on few tiles a rule is an upper bound.
+
 The norm of a red-black solve's check: its blocks fit one launch dimension and
 the partials of its points, thin grids and the largest among them."""
 import os
@@ -80,6 +83,43 @@ int main() {
 }
 """
 
+SHARE = r"""
+#include <stdio.h>
+#include <vector>
+#include "tb7.h"
+using namespace gk;
+
+int main() {
+    long seen = 0, bad = 0;
+    for (int n : {1, 3, 8, 17, 64, 300})
+        for (int side : {1, 12, 40, 80, 176})
+            for (int rule : {1, 4, 16, 32, 500})
+                for (int lay = 0; lay < 4; ++lay) {
+                    const bool rb = lay & 1, f64 = lay & 2;
+                    std::vector<TBShare> a, b;
+                    long tiles = 0;
+                    for (int i = 0; i < n; ++i) {
+                        const int nz = side + i % 7, cols = (nz + 55) / 56 * ((nz + 23) / 24), own = i % 5 ? rule : 0;
+                        a.push_back({cols, nz, own, 0});
+                        b.push_back({cols, nz, 0, 0});
+                        const int c = own < 1 ? (nz < 16 ? nz : 16) : own < nz ? own : nz;
+                        tiles += (long)cols * ((nz + c - 1) / c);
+                    }
+                    tb_share_chunks(a.data(), n, rb, f64, 4);
+                    tb_share_chunks(b.data(), n, rb, f64, 4);
+                    for (int i = 0; i < n; ++i) {
+                        ++seen;
+                        bad += a[i].cz < 1 || a[i].cz > a[i].nz || b[i].cz < 1 || b[i].cz > b[i].nz;
+                        const int own = rule < a[i].nz ? rule : a[i].nz;
+                        if (tiles >= 512) bad += a[i].cz != (a[i].rule && own > b[i].cz ? own : b[i].cz);
+                        else if (a[i].rule) bad += a[i].cz > own;
+                    }
+                }
+    printf("%ld %ld\n", seen, bad);
+    return 0;
+}
+"""
+
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
@@ -105,3 +145,9 @@ def test_admitted_reductions_fit_the_fixed_scratch(tmp_path):
 def test_norm_blocks_fit_a_launch(tmp_path):
     seen, bad = _run(tmp_path, NORM)
     assert bad == 0 and seen > 100
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_rules_bound_the_chunks_of_a_batch(tmp_path):
+    seen, bad = _run(tmp_path, SHARE)
+    assert bad == 0 and seen > 1000
