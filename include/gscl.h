@@ -349,6 +349,8 @@ int gscl_do_reduce(gscl_ctx *ctx, const gscl_reduce_desc *rd, const gscl_grid *a
 typedef struct { int32_t V, NW, cz; } gscl_tile;
 int gscl_tile_get(gscl_ctx *ctx, int kind, const gscl_grid_desc *grid, gscl_tile *out);
 int gscl_tile_set(gscl_ctx *ctx, int kind, const gscl_grid_desc *grid, const gscl_tile *tile);
+/* Back to the library's own choice for one (kind, dtype, extents) key. */
+int gscl_tile_unset(gscl_ctx *ctx, int kind, const gscl_grid_desc *grid);
 int gscl_tile_clear(gscl_ctx *ctx);
 
 /* ---- HIP graphs of library launches --------------------------------------- */

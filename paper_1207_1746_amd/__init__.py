@@ -105,6 +105,7 @@ _SIGS = {
     "gscl_do_reduce": (ctypes.c_int, [_vp, _P(ReduceDesc), _vp, _vp, _P(_f64)]),
     "gscl_tile_get": (ctypes.c_int, [_vp, ctypes.c_int, _P(GridDesc), _P(Tile)]),
     "gscl_tile_set": (ctypes.c_int, [_vp, ctypes.c_int, _P(GridDesc), _P(Tile)]),
+    "gscl_tile_unset": (ctypes.c_int, [_vp, ctypes.c_int, _P(GridDesc)]),
     "gscl_tile_clear": (ctypes.c_int, [_vp]),
     "gscl_graph_begin": (ctypes.c_int, [_vp]),
     "gscl_graph_end": (ctypes.c_int, [_vp, _P(_vp)]),
@@ -437,6 +438,9 @@ class Context:
     def tile_set(self, kind: int, g: Grid, tile: tuple):
         t = Tile(*tile)
         check(lib().gscl_tile_set(self.handle, kind, ctypes.byref(g.desc), ctypes.byref(t)), "gscl_tile_set")
+
+    def tile_unset(self, kind: int, g: Grid):
+        check(lib().gscl_tile_unset(self.handle, kind, ctypes.byref(g.desc)), "gscl_tile_unset")
 
     def tile_clear(self):
         check(lib().gscl_tile_clear(self.handle), "gscl_tile_clear")

@@ -1,13 +1,16 @@
 """Tile autotuner for the tiled do_all kernels (autotuning is the paper's
 stated future work, Section 2 and Section 6).
 
-For one operator kind and one set of grid extents it times every candidate
-tile shape (V elements per lane, NW waves per block, cz planes per block) with
-HIP events, keeps the fastest, installs it in the context with
-``gscl_tile_set`` and records it in a JSON cache keyed by
-(gfx arch, kind, dtype, extents).  Outputs do not depend on the tile shape
-(only the fused-reduction rounding order does), so tuning never changes a
-do_all result.
+For one operator kind and one set of grid extents it times the library's own
+choice and every candidate tile shape (V elements per lane, NW waves per block,
+cz planes per block) with HIP events.  A candidate that beats the library's
+choice by more than the timings' spread is installed in the context with
+``gscl_tile_set``; otherwise the choice stays with the library, which for the
+blocked kinds balances each launch and for small images takes another kernel.
+The outcome is recorded in a JSON cache keyed by (gfx arch, kind, dtype,
+extents; the blocked kinds also by their levels).  Outputs do not depend on the
+tile shape (only the fused-reduction rounding order does), so tuning never
+changes a do_all result.
 
 For the batched executor it picks, per request-size bucket, the z chunks of
 the one-sweep and blocked-pass tiles (``gscl_batch_tile_rule``) by timing
@@ -39,10 +42,10 @@ BATCH_BUCKETS = ((48, 40), (96, 80), (144, 128), (192, 176))
 def candidates(kind: int, dtype: int, nz: int) -> list[tuple[int, int, int]]:
     """Tile shapes that have an instantiated kernel for this kind and dtype."""
     if kind == G.K_IMG_BOX5_LAP:
-        return [(4, 4, cy) for cy in (4, 8, 16, 32, 64)]
+        return [(4, 4, cy) for cy in (1, 2, 4, 8, 16, 32, 64)]
     if kind in BLOCKED:
         # fixed block shape: only the z chunk (output planes) varies
-        return [(1, 16, cz) for cz in (1, 2, 4, 8, 16, 32, 64) if cz <= max(nz, 1)]
+        return [(1, 16, cz) for cz in (1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64) if cz <= max(nz, 1)]
     if kind in RADIUS2:
         # one-field operators run NW = 4 only; shapes without a kernel are
         # skipped by the tuner (the launch reports them as unsupported)
@@ -55,9 +58,14 @@ def candidates(kind: int, dtype: int, nz: int) -> list[tuple[int, int, int]]:
     return [(v, nw, cz) for v, nw, cz in itertools.product(vs, nws, czs)]
 
 
-def _key(arch: str, kind: int, g: "G.Grid") -> str:
+def _key(arch: str, kind: int, g: "G.Grid", p: Sequence[float] = ()) -> str:
     d = g.desc
-    return f"{arch}|{kind}|{d.dtype}|{d.n[0]}x{d.n[1]}x{d.n[2]}"
+    key = f"{arch}|{kind}|{d.dtype}|{d.n[0]}x{d.n[1]}x{d.n[2]}"
+    if kind in BLOCKED:  # the levels of a pass: the last parameter; 4 where it is not known
+        at = 2 if kind == G.K_WJACOBI_TB else 3
+        key += f"|k{int(p[at]) if len(p) > at else 4}"
+    # (kinds whose tiles mean something else than in earlier records)
+    return key + "|r2" if kind in BLOCKED or kind == G.K_IMG_BOX5_LAP else key
 
 
 def _arch() -> str:
@@ -96,40 +104,62 @@ class Tuner:
 
     def tune(self, kind: int, ins: Sequence["G.Grid"], outs: Sequence["G.Grid"], p: Iterable[float] = (),
              terms=None, cands: list | None = None, reps: int = 10, force: bool = False) -> dict:
-        """Pick the fastest tile for do_all(kind, ins, outs, p) and install it."""
+        """Pick the fastest tile for do_all(kind, ins, outs, p) and install it
+        (none where the library's own choice is as fast: record "own").  A chunk
+        installed for a blocked kind holds for every number of levels."""
         ref = ins[0]
-        key = _key(self.arch, kind, ref)
-        if not force and key in self.table:
-            rec = self.table[key]
-            self.ctx.tile_set(kind, ref, tuple(rec["tile"]))
-            return rec
         p = tuple(p)
+        key = _key(self.arch, kind, ref, p)
+        if not force and key in self.table:
+            self._install(kind, ref, self.table[key])
+            return self.table[key]
         cands = cands or candidates(kind, ref.desc.dtype, ref.desc.n[2])
+
+        def time_it():
+            try:
+                return time_call(lambda: self.ctx.do_all(kind, ins, outs, p=p, terms=terms), reps=reps,
+                                 stream=self.ctx.stream)
+            except G.GsclError:  # no kernel for the shape
+                return None
+
+        self.ctx.tile_unset(kind, ref)
+        own_tile, own = self.ctx.tile_get(kind, ref), time_it()
         results = []
         for tile in cands:
             self.ctx.tile_set(kind, ref, tile)
-            try:
-                ms = time_call(lambda: self.ctx.do_all(kind, ins, outs, p=p, terms=terms), reps=reps,
-                               stream=self.ctx.stream)
-            except G.GsclError:
-                continue
-            results.append((ms, tile))
-        if not results:
+            ms = time_it()
+            if ms is not None:
+                results.append((ms, tile))
+        if own is None or not results:
+            self.ctx.tile_unset(kind, ref)
             raise RuntimeError("no tile candidate ran")
         results.sort()
         ms, tile = results[0]
-        self.ctx.tile_set(kind, ref, tile)
-        rec = {"tile": list(tile), "us": ms * 1e3,
-               "tried": [[list(t), round(m * 1e3, 2)] for m, t in results]}
+        # the same call timed twice differs by up to some percent
+        keep = ms > 0.97 * own
+        rec = {"tile": list(own_tile if keep else tile), "us": (own if keep else ms) * 1e3, "own": keep,
+               "own_us": round(own * 1e3, 2), "tried": [[list(t), round(m * 1e3, 2)] for m, t in results]}
+        self._install(kind, ref, rec)
         self.table[key] = rec
         return rec
 
-    def apply(self, kind: int, grid: "G.Grid") -> bool:
-        """Install a cached tile for (kind, grid extents) if there is one."""
-        rec = self.table.get(_key(self.arch, kind, grid))
-        if rec:
+    def _install(self, kind: int, grid: "G.Grid", rec: dict):
+        if rec.get("own"):
+            self.ctx.tile_unset(kind, grid)
+        else:
             self.ctx.tile_set(kind, grid, tuple(rec["tile"]))
-            return True
+
+    def apply(self, kind: int, grid: "G.Grid", p: Sequence[float] = ()) -> bool:
+        """Install the cached outcome for (kind, grid extents; blocked kinds: the
+        levels in p, else 4 or the most there is a record for) if there is one."""
+        keys = [_key(self.arch, kind, grid, p)]
+        if kind in BLOCKED and not len(p):
+            keys = [_key(self.arch, kind, grid, (0, 0, k) if kind == G.K_WJACOBI_TB else (0, 0, 0, k))
+                    for k in (4, 3, 2, 1)]
+        for key in keys:
+            if key in self.table:
+                self._install(kind, grid, self.table[key])
+                return True
         return False
 
     def tune_batch(self, precision: int = G.PREC_F32_IR, method: int = G.BATCH_JACOBI,

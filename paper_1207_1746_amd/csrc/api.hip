@@ -336,6 +336,15 @@ extern "C" int gscl_tile_get(gscl_ctx* c, int kind, const gscl_grid_desc* gd, gs
     return GSCL_OK;
 }
 
+extern "C" int gscl_tile_unset(gscl_ctx* c, int kind, const gscl_grid_desc* gd) {
+    if (!ctx_ok(c) || !gd) return gscl_fail(GSCL_ERR_ARG, "invalid argument");
+    gscl_grid_desc d = *gd;
+    int rc = resolve_layout(&d);
+    if (rc) return rc;
+    c->tiles.erase(std::make_tuple(kind, d.dtype, d.n[0], d.n[1], d.n[2]));
+    return GSCL_OK;
+}
+
 extern "C" int gscl_tile_clear(gscl_ctx* c) {
     if (!ctx_ok(c)) return gscl_fail(GSCL_ERR_ARG, "invalid context");
     c->tiles.clear();
