@@ -354,7 +354,7 @@ extern "C" int gscl_tile_clear(gscl_ctx* c) {
 // ---------------------------------------------------------------------------
 // do_all validation and dispatch
 // ---------------------------------------------------------------------------
-static bool overlaps(const gscl_grid* a, const gscl_grid* b) {
+bool overlaps(const gscl_grid* a, const gscl_grid* b) {
     const char* pa = (const char*)a->ptr;
     const char* pb = (const char*)b->ptr;
     return pa < pb + b->bytes && pb < pa + a->bytes;

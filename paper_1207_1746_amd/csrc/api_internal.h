@@ -57,3 +57,4 @@ int ensure_partials(gscl_ctx* c, int64_t nblocks);
 gk::TileCfg pick_tile(gscl_ctx* c, int kind, int dtype, const gscl_grid_desc& d);
 bool ctx_ok(const gscl_ctx* c);
 bool grid_ok(const gscl_grid* g);
+bool overlaps(const gscl_grid* a, const gscl_grid* b);  // their address ranges

@@ -35,6 +35,9 @@ bool blocked_passes(const gscl_grid_desc& d) {
     return ((d.n[1] - 1) * d.pitch[0] + d.n[0]) * (int64_t)sizeof(double) <= (int64_t)UINT32_MAX;
 }
 
+// Grids of 72^3 points and more have always run blocked passes.
+bool large_grid(const gscl_grid_desc& d) { return d.n[0] * d.n[1] * d.n[2] >= (int64_t)72 * 72 * 72; }
+
 // Workspace that a red-black solve cannot do without, below which it is
 // refused; without room for the ping-pong grid of blocked passes on top, its
 // colour passes run in place.
@@ -110,8 +113,7 @@ struct Cleanup {
 };
 
 size_t rbgs_least_bytes(const gscl_grid_desc& d) {
-    const bool large = d.n[0] * d.n[1] * d.n[2] >= (int64_t)72 * 72 * 72;
-    return bytes_like(d, GSCL_F32) + (large && blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
+    return bytes_like(d, GSCL_F32) + (large_grid(d) && blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
 }
 
 }  // namespace
@@ -336,10 +338,13 @@ extern "C" int gscl_solve(gscl_ctx* c, const gscl_solve_desc* sd, gscl_grid* con
         for (int f = 0; f < nf; ++f) w[f] = carve(c, xd, GSCL_F64, R, cur, cl.grids);
         const int S = sd->check_every;
         // A chunk of S sweeps is a sequence of passes over memory.  Poisson
-        // chunks on large grids run temporally blocked passes of up to TB_KMAX
-        // sweeps (the same sweeps bit for bit, fewer passes); elsewhere every
-        // pass is one sweep.  The pass count is kept even so the chunk ends in x.
-        const bool tb = poisson && blocked_passes(xd);
+        // chunks run temporally blocked passes of up to TB_KMAX sweeps (the same
+        // sweeps bit for bit, fewer passes); elsewhere every pass is one sweep.
+        // The pass count is kept even so the chunk ends in x.  A blocked pass
+        // takes no right-hand side inside its output's address range (b and x as
+        // columns of one array): small grids then keep plain sweeps, which read
+        // it at the point they write.
+        const bool tb = poisson && blocked_passes(xd) && (large_grid(xd) || !overlaps(x[0], b[0]));
         const std::vector<int> passes = tb ? split_passes(S) : std::vector<int>(S, 1);
         // x -> w -> x ...; the last pass also reduces the residual of its input
         auto pass = [&](size_t q) -> int {
