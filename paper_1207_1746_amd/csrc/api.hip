@@ -137,7 +137,6 @@ extern "C" int gscl_init(int device, gscl_ctx** out) {
     c->stream = nullptr;
     c->partials = nullptr;
     c->partial_cap = 0;
-    c->result = nullptr;
     c->host_result = nullptr;
     c->capturing = false;
     *out = c;
@@ -196,14 +195,10 @@ extern "C" int gscl_begin(gscl_ctx* c, void* stream) {
     int src = scratch_setup(c->device);
     if (src) return src;
     c->stream = (hipStream_t)stream;
-    if (!c->result) {
-        if (!c->host_result)
-            GSCL_HIP(hipHostMalloc((void**)&c->host_result, 64 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
-        GSCL_HIP(hipMalloc(&c->result, 64 * sizeof(double)));
-        GSCL_HIP(hipMemset(c->result, 0, 64 * sizeof(double)));
-        int rc = ensure_partials(c, 1 << 16);
-        if (rc) return rc;
-    }
+    if (!c->host_result)
+        GSCL_HIP(hipHostMalloc((void**)&c->host_result, 64 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
+    int rc = ensure_partials(c, 1 << 16);
+    if (rc) return rc;
     c->state = CTX_ACTIVE;
     return GSCL_OK;
 }
@@ -228,10 +223,9 @@ extern "C" int gscl_end(gscl_ctx* c) {
 extern "C" int gscl_finalize(gscl_ctx* c) {
     if (!ctx_ok(c)) return gscl_fail(GSCL_ERR_ARG, "invalid context");
     if (c->state == CTX_ACTIVE) return gscl_fail(GSCL_ERR_STATE, "gscl_finalize inside begin/end");
-    if (c->result) {
+    if (c->partials) {
         hipSetDevice(c->device);
         hipFree(c->partials);
-        hipFree(c->result);
     }
     if (c->host_result) hipHostFree(c->host_result);
     c->magic = 0;

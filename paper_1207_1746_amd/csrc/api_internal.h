@@ -19,7 +19,6 @@ struct gscl_ctx {
     hipStream_t stream;
     double* partials;      // per-block reduction partials
     int64_t partial_cap;   // doubles
-    double* result;        // device slots for reduction results
     double* host_result;   // pinned host slots that kernels write: results the host waits for
     bool capturing;
     std::map<std::tuple<int, int, int64_t, int64_t, int64_t>, gk::TileCfg> tiles;

@@ -38,9 +38,9 @@ bool blocked_passes(const gscl_grid_desc& d) {
 // Grids of 72^3 points and more have always run blocked passes.
 bool large_grid(const gscl_grid_desc& d) { return d.n[0] * d.n[1] * d.n[2] >= (int64_t)72 * 72 * 72; }
 
-// Workspace that a red-black solve cannot do without, below which it is
-// refused; without room for the ping-pong grid of blocked passes on top, its
-// colour passes run in place.
+// Workspace below which a red-black solve is refused: the ping-pong grid of
+// blocked passes on large grids; half of that on small ones, whose colour passes
+// run in place without room for it.
 size_t rbgs_least_bytes(const gscl_grid_desc& d);
 
 // Split n sweeps (or colour passes) into passes of at most TB_KMAX, with an
@@ -113,7 +113,7 @@ struct Cleanup {
 };
 
 size_t rbgs_least_bytes(const gscl_grid_desc& d) {
-    return bytes_like(d, GSCL_F32) + (large_grid(d) && blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
+    return bytes_like(d, large_grid(d) && blocked_passes(d) ? GSCL_F64 : GSCL_F32) + 256;
 }
 
 }  // namespace
@@ -121,7 +121,7 @@ size_t rbgs_least_bytes(const gscl_grid_desc& d) {
 extern "C" size_t gscl_solve_workspace_bytes(const gscl_solve_desc* sd, const gscl_grid* x, int nf) {
     if (!sd || !grid_ok(x) || nf < 1) return 0;
     const gscl_grid_desc& d = x->d;
-    if (sd->kind == GSCL_K_RBGS)  // the ping-pong grid of blocked passes, and what the least counts
+    if (sd->kind == GSCL_K_RBGS)  // the ping-pong grid of blocked passes, and an F32 grid spare
         return bytes_like(d, GSCL_F32) + (blocked_passes(d) ? bytes_like(d, GSCL_F64) : 0) + 256;
     if (sd->precision == GSCL_PREC_F64) return bytes_like(d, GSCL_F64) * nf + 256;
     const int s = inner_dtype(sd->precision);
