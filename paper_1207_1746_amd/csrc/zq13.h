@@ -122,7 +122,7 @@ __device__ __forceinline__ ColSrc<V> col_src(const Geo& g, int gx) {
     for (int i = 0; i < V; ++i) {
         const int x = gx + i;
         const bool in = (unsigned)x < (unsigned)g.nx;
-        c.xi[i] = in ? x : wrap_idx(x, g.nx, xbc);
+        c.xi[i] = in ? x : wrap_mod(x, g.nx, xbc);
         c.xv[i] = in || g.bc != BC_DIRICHLET;
     }
     return c;
@@ -194,8 +194,8 @@ __global__ __launch_bounds__(64 * NW) void zq13_sweep(TArgs a) {
 
     // rows (wave-uniform): the core row and the y-halo row this wave stages
     const bool yc_in = (unsigned)gy < (unsigned)g.ny, yh_in = (unsigned)hy < (unsigned)g.ny;
-    const uint32_t yc_off = (uint32_t)(yc_in ? gy : wrap_idx(gy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
-    const uint32_t yh_off = (uint32_t)(yh_in ? hy : wrap_idx(hy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
+    const uint32_t yc_off = (uint32_t)(yc_in ? gy : wrap_mod(gy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
+    const uint32_t yh_off = (uint32_t)(yh_in ? hy : wrap_mod(hy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
     const bool yc_ok = yc_in || !dir, yh_ok = yh_in || !dir;
     // pointwise grids: rows past the interior read a valid row (results unused)
     const uint32_t ypw_off = (uint32_t)min(gy, g.ny - 1) * py;
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) void zq13_sweep(TArgs a) {
     auto zsrc = [&](int z, bool& ok) __attribute__((always_inline)) -> uint32_t {
         const bool in = (unsigned)z < (unsigned)g.nz;
         ok = in || !dir;
-        return (uint32_t)(in ? z : wrap_idx(z, g.nz, dir ? BC_CLAMP : g.bc)) * pz;
+        return (uint32_t)(in ? z : wrap_mod(z, g.nz, dir ? BC_CLAMP : g.bc)) * pz;
     };
     auto load_core = [&](int z, RN (&dst)[NF]) __attribute__((always_inline)) {
         bool zok;

@@ -78,8 +78,8 @@ __global__ __launch_bounds__(64 * NW) void zqw_sweep(TArgs a) {
     const uint32_t pz = (uint32_t)g.pz, py = (uint32_t)g.py;
 
     const bool yc_in = (unsigned)gy < (unsigned)g.ny, yh_in = (unsigned)hy < (unsigned)g.ny;
-    const uint32_t yc_off = (uint32_t)(yc_in ? gy : wrap_idx(gy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
-    const uint32_t yh_off = (uint32_t)(yh_in ? hy : wrap_idx(hy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
+    const uint32_t yc_off = (uint32_t)(yc_in ? gy : wrap_mod(gy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
+    const uint32_t yh_off = (uint32_t)(yh_in ? hy : wrap_mod(hy, g.ny, dir ? BC_CLAMP : g.bc)) * py;
     const bool yc_ok = yc_in || !dir, yh_ok = yh_in || !dir;
     const uint32_t ypw_off = (uint32_t)min(gy, g.ny - 1) * py;
     const uint32_t xpw = gx < g.nx ? (uint32_t)gx : 0u;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * NW) void zqw_sweep(TArgs a) {
     auto zsrc = [&](int z, bool& ok) __attribute__((always_inline)) -> uint32_t {
         const bool in = (unsigned)z < (unsigned)g.nz;
         ok = in || !dir;
-        return (uint32_t)(in ? z : wrap_idx(z, g.nz, dir ? BC_CLAMP : g.bc)) * pz;
+        return (uint32_t)(in ? z : wrap_mod(z, g.nz, dir ? BC_CLAMP : g.bc)) * pz;
     };
     auto bc_word = [&]() __attribute__((always_inline)) -> W {
         RawE<SN> e[V];
