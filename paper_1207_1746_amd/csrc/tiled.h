@@ -393,6 +393,12 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
 template <class Op, int V, int NW, bool RED>
 __global__ __launch_bounds__(64 * NW) void tiled_sweep(TArgs a) {
     const int ntiles = a.ntx * a.nty * a.ncz;
+    // The arguments of the first loads, requested together: the set-up's blocks
+    // would else each wait for their own, one after the other (64^3 VARCOEF7
+    // FP64, Dirichlet, 8.0 -> 7.7 us a sweep).
+    if constexpr (Op::NF == 1)
+        asm volatile("" ::"s"(a.nb[0]), "s"(a.pa[0]), "s"(a.g.pz), "s"(a.g.py), "s"(a.g.bc), "s"(a.g.bcv), "s"(a.g.nz),
+                     "s"(a.cz), "s"(a.out[0]));
     const int tile = xcd_remap(blockIdx.x, ntiles);
     double acc = 0.0;
     sweep_tile<Op, V, NW, RED>(a, tile, acc);
