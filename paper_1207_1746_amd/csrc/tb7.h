@@ -10,7 +10,7 @@
 // others a shift away (a shift across the halves only fills ghost columns): half
 // the shifts, but twice the registers per lane, which in FP64 leave Jacobi two
 // waves per SIMD (1.5 us a step of 4 levels; four rows of one column 1.47; 16
-// waves of two rows 1.35).  The y neighbour inside the two rows is in the lane,
+// waves of two rows 1.37).  The y neighbour inside the two rows is in the lane,
 // and only the row of the next group up or down goes through LDS.  The region is
 // the output tile grown by k cells on every side (pairs: columns by k rounded up
 // to even): level t (the grid after t sweeps) is needed on the tile grown by
