@@ -345,7 +345,8 @@ int gscl_do_reduce(gscl_ctx *ctx, const gscl_reduce_desc *rd, const gscl_grid *a
  * GSCL_K_WJACOBI_TB and GSCL_K_RBGS_TB have a fixed block shape (V = 1,
  * NW = 16: 32 rows): gscl_tile_set takes only their cz and gscl_tile_get
  * reports it so; with no cz set it reports a nominal chunk, and a launch picks
- * the chunk that balances its blocks over the CUs. */
+ * the chunk that balances its blocks over the CUs.  GSCL_K_IMG_BOX5_LAP: cz is
+ * the rows a wave filters; with none set, small images take a thread per pixel. */
 typedef struct { int32_t V, NW, cz; } gscl_tile;
 int gscl_tile_get(gscl_ctx *ctx, int kind, const gscl_grid_desc *grid, gscl_tile *out);
 int gscl_tile_set(gscl_ctx *ctx, int kind, const gscl_grid_desc *grid, const gscl_tile *tile);
