@@ -100,9 +100,9 @@ constexpr int MAX_SLOTS = 64 * 64;  // (find_slot's two looks)
 // slot is not running.  The lanes look at 64 slots together, after one look at
 // every 64th slot where there are more: a table holds at most 64 x 64 slots.
 // (A chain of dependent loads, each longer than a step of the march: a binary
-// search takes up to 12, a scan 64 at a time up to 64 pairs.  4096 requests of 12^3, plain passes, ms
-// a step of 64 sweeps: 15.9 by binary search, 54.6 by the scan, 14.8 so; 1024 of
-// 16^3, blocked FP32 passes: 1.43, 1.54, 1.29.)
+// search takes up to 12, a scan 64 at a time up to 64 pairs.  4096 requests of
+// 12^3, plain passes, ms a step of 64 sweeps: 15.9 by binary search, 54.6 by the
+// scan, 14.8 so; 1024 of 16^3, blocked FP32 passes: 1.43, 1.54, 1.29.)
 template <int LIST>
 __device__ __forceinline__ int find_slot(const BFind* __restrict__ s, const BState* st, int n, int t, int& local) {
     const int lane = threadIdx.x & 63;
@@ -366,6 +366,7 @@ struct gscl_batch {
     BHeader* d_hdr;
     double* d_partials;
     int64_t partial_cap;
+    std::vector<gk::TBShare> share;  // chunks of the blocked passes
     BSlot* h_slots;     // pinned staging
     BFind* h_find;      // pinned staging
     BState* h_state;    // pinned
@@ -512,6 +513,7 @@ extern "C" int gscl_batch_create(gscl_ctx* c, const gscl_batch_desc* bd, gscl_ba
     b->admit_step.assign(ms, 0);
     b->known_state.assign(ms, 0);
     b->slot.assign(ms, BSlot{});
+    b->share.reserve(ms);
     b->work_bytes.assign(ms, 0);
     b->work_ptr.assign(ms, nullptr);
     b->foot.assign(ms, 0);
@@ -551,7 +553,8 @@ static void set_tb_tiles(BSlot& s, int kp, bool pairs) {
 // Blocked tiles of the passes without a reduction, whose tiling changes no
 // result: the slots share one launch.
 static void balance_tb_tiles(gscl_batch* b) {
-    std::vector<gk::TBShare> share;
+    auto& share = b->share;  // (holds max_slots: nothing is allocated here)
+    share.clear();
     for (int id = 0; id < b->desc.max_slots; ++id)
         if (b->used[id]) share.push_back({tb_cols(b->slot[id]), b->slot[id].nz, b->slot[id].rule_cz, 0});
     gk::tb_share_chunks(share.data(), (int)share.size(), b->desc.method == GSCL_BATCH_RBGS,
