@@ -213,8 +213,19 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
 #pragma unroll
     for (int s = 0; s < (PF ? QD : QD - 1); ++s)
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
-            load_core(f, z0 - RZ + s, q[f][s]);
+        for (int f = 0; f < NF; ++f) {
+            const int z = z0 - RZ + s;
+            if (V == 1 && PF && s < QD - 1) {
+                // loaded where inside instead of replaced where outside, which would
+                // wait for these planes before the first step's loads (53 x 42 x 107
+                // VARCOEF7, Dirichlet: FP32 7.55 -> 7.20 us a sweep, FP64 10.0 -> 9.75)
+                q[f][s][0] = bcv;
+                if ((yc_ok && z_ok(z)) && __builtin_amdgcn_inverse_ballot_w64(km[0]))
+                    q[f][s][0] = from_s<T>(*row_at(static_cast<const SN*>(a.nb[f]) + (z_off(z) + yc_off), xi[0]));
+            } else {
+                load_core(f, z, q[f][s]);
+            }
+        }
     if (PF) {
         load_halo(z0, xh, yh);
         load_point(z0, pa, pb);
@@ -222,7 +233,8 @@ __device__ __forceinline__ void sweep_tile(const TArgs& a, const int tile, doubl
 #pragma unroll
     for (int s = 0; s < QD - 1; ++s)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) bound_core(z0 - RZ + s, q[f][s]);
+        for (int f = 0; f < NF; ++f)
+            if (V > 1 || !PF) bound_core(z0 - RZ + s, q[f][s]);
 
     const bool row_ok = gy < g.ny;
 
